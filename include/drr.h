@@ -66,18 +66,30 @@ extern "C" {
                              gathers use 32-bit byte offsets), a detector of more than
                              2^30 pixels, or more than 2^31 - 1 tiles in one launch */
 
-/* Memory layouts of the packed volume.  Both hold the voxels surrounded by a
- * one-voxel border of zeros and give bitwise identical renders; they differ
- * in speed only.
+/* Memory layouts of the packed volume.  Each holds the voxels surrounded by
+ * a one-voxel border of zeros.
  *   DRR_LAYOUT_INPUT     one copy in the caller's order (z fastest).
  *   DRR_LAYOUT_PER_AXIS  three copies, one per principal ray axis: a pose
  *                        whose central ray runs mostly along axis c reads the
  *                        copy whose fastest-varying memory axis is the
  *                        finer-spaced of the two other axes, so that the
  *                        rays of neighbouring detector pixels gather from
- *                        shared cache lines.  Three times the memory. */
+ *                        shared cache lines; and crossing tables (some 24
+ *                        bytes a voxel), from which renders are made in about
+ *                        half the time.
+ *   DRR_LAYOUT_INPUT | DRR_LAYOUT_CROSSINGS  one copy and the tables.
+ * Volumes too large for the tables' 32-bit offsets (a table of 3.5 GiB, some
+ * 900 million voxels) are packed without them.  Renders are bitwise identical
+ * between the layouts that have tables, and between those that have not;
+ * with and without tables they differ by their rounding only (some 1e-9 of a
+ * pixel; the tables hold sums of voxels to 2^-31 of the largest difference
+ * between neighbouring columns of voxels).  Where that would be felt -- a
+ * volume in which that difference exceeds 32 mean column sums, or with a
+ * voxel that is not finite -- the tables are marked as unusable when the
+ * volume is packed, and renders are made from the copies. */
 #define DRR_LAYOUT_INPUT 0
 #define DRR_LAYOUT_PER_AXIS 1
+#define DRR_LAYOUT_CROSSINGS 0x100
 
 typedef struct drr_volume_desc {
     int32_t nx, ny, nz;   /* voxels per axis, each >= 1 */

@@ -138,6 +138,7 @@ def call(func: str, *args):
 
 DRR_LAYOUT_INPUT = 0
 DRR_LAYOUT_PER_AXIS = 1
+DRR_LAYOUT_CROSSINGS = 0x100
 
 
 def volume_desc(shape, spacing, origin, layout=DRR_LAYOUT_INPUT) -> VolumeDesc:

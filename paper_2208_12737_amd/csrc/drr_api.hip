@@ -86,6 +86,29 @@ static int32_t launch_flat(const void* packed, const drr_volume_desc& vol,
     // of at most one workgroup per CU (a single DRR of up to 256 x 256
     // pixels) leave each SIMD one wave and take the deepest pipeline
     const uint64_t cus = (uint64_t)num_cus();
+    if (has_run_tables(vol)) {
+        // tiles of 8 x 8-pixel waves (batches 1-4% and odd views up to 15%
+        // faster than 4 x 16-pixel waves: the rays of a wave read fewer rows)
+        auto launch = [&](auto kernel, int tiles, int wgs) {
+            const uint64_t rows = ((uint64_t)g.tiles_y + tiles - 1) / tiles;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)(rows * g.tiles_x * n_poses)),
+                               dim3(256 * tiles),
+                               occupancy_lds(wgs, tile_sum_lds_bytes(ModeTraits<MODE>::nsum, 4 * tiles)),
+                               stream, vol_args(packed, vol), det_args(det), poses, g.tiles_x,
+                               g.tiles_y, image, jac, counts, aux, aux_stride, partials);
+            return check_launch("render kernel launch");
+        };
+        const int set = g_wg_per_cu.load(std::memory_order_relaxed);
+        // (two concurrent launches of 512 tiles each, of a registration in two
+        // chains, are 12% slower with the reads of RunFew)
+        if (blocks <= cus)
+            return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFew>, 1, set >= 0 ? set : 4);
+        const int wgs = run_big_tables(vol, det);
+        if (wgs == 0 || blocks <= 8ull * cus)
+            return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull>, 1, set >= 0 ? set : 4);
+        return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull, 2>, 2,
+                      set >= 0 ? (set + 1) / 2 : wgs);
+    }
     if constexpr (MODE == kImage || MODE == kCount) {
         // per-pixel results that do not depend on the launch shape: a launch
         // of at most one workgroup per CU uses 8 x 8-pixel waves (16 x 16
@@ -96,21 +119,22 @@ static int32_t launch_flat(const void* packed, const drr_volume_desc& vol,
         const uint64_t tb = (uint64_t)tx * (uint64_t)((det.height + TS::px_h - 1) / TS::px_h) *
                             (uint64_t)n_poses;
         if (tb <= cus) {
-            hipLaunchKernelGGL((render_flat<8, 2, 2, MODE, kTinyDepth>), dim3((unsigned)tb),
+            hipLaunchKernelGGL((render_flat<8, 2, 2, MODE, kTinyDepth, void>), dim3((unsigned)tb),
                                dim3(TS::threads), 0, stream, vol_args(packed, vol), det_args(det),
-                               poses, tx, (int)(tb / (uint64_t)n_poses), image, jac, counts, aux,
-                               aux_stride, partials);
+                               poses, tx, (int)(tb / (uint64_t)n_poses) / tx, image, jac, counts,
+                               aux, aux_stride, partials);
             return check_launch("render kernel launch");
         }
     }
-    auto kernel = blocks <= cus ? render_flat<kTW, kWX, kWY, MODE, kTinyDepth>
-                  : blocks <= 16ull * cus ? render_flat<kTW, kWX, kWY, MODE, kDeepDepth>
-                                          : render_flat<kTW, kWX, kWY, MODE, full_depth<MODE>()>;
+    auto kernel = blocks <= cus ? render_flat<kTW, kWX, kWY, MODE, kTinyDepth, void>
+                  : blocks <= 16ull * cus
+                      ? render_flat<kTW, kWX, kWY, MODE, kDeepDepth, void>
+                      : render_flat<kTW, kWX, kWY, MODE, full_depth<MODE>(), void>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks),
                        dim3(DefaultShape::threads),
                        occupancy_lds(wg_per_cu_for(vol), flat_static_lds<MODE>()), stream,
                        vol_args(packed, vol),
-                       det_args(det), poses, g.tiles_x, g.wg_per_pose, image, jac, counts, aux,
+                       det_args(det), poses, g.tiles_x, g.tiles_y, image, jac, counts, aux,
                        aux_stride, partials);
     return check_launch("render kernel launch");
 }
@@ -184,7 +208,43 @@ const char* drr_status_string(int32_t s)
 size_t drr_volume_packed_bytes(const drr_volume_desc* vol)
 {
     if (validate_volume(vol) != DRR_OK) return 0;
+    if (has_run_tables(*vol))
+        return (size_t)(run_header_offset(*vol) + run_table_offset(*vol, 3, 0));
     return (size_t)(packed_elems(*vol) * 4ull);
+}
+
+// Fills the crossing tables behind the copies.
+static int32_t pack_run_tables(const float* src, void* packed, const drr_volume_desc& vol,
+                               hipStream_t s)
+{
+    const int n[3] = {vol.nx, vol.ny, vol.nz};
+    const int64_t pitch[3] = {(int64_t)vol.ny * vol.nz, vol.nz, 1};
+    char* base = (char*)packed + run_header_offset(vol);
+    RunHeader* h = (RunHeader*)base;
+    hipLaunchKernelGGL(k_run_clear, dim3(1), dim3(64), 0, s, h);
+    for (int pass = 0; pass < 3; ++pass) {
+        if (pass == 2) hipLaunchKernelGGL(k_run_quanta, dim3(1), dim3(64), 0, s, h, n[0], n[1], n[2]);
+        for (int q = 0; q < 3; ++q) {
+            double2* ends = (double2*)(base + run_table_offset(vol, q, 2));
+            const int lo = q == 0 ? 1 : 0, hi = q == 2 ? 1 : 2;
+            for (int w = 0; w < (pass == 0 ? 1 : 2); ++w) {
+                // strips along the axis whose planes the table holds
+                const int a = w ? hi : lo, b = w ? lo : hi;
+                auto scan = pass == 0 ? k_run_scan<0> : (pass == 1 ? k_run_scan<1> : k_run_scan<2>);
+                hipLaunchKernelGGL(scan, dim3(n[b], (n[a] + kRunCols) / kRunCols), dim3(256), 0, s,
+                                   src, h, q, ends, w == 0,
+                                   (int*)(base + run_table_offset(vol, q, w)), n[a], n[b], n[q],
+                                   pitch[a], pitch[b], pitch[q], (int64_t)(w ? 1 : n[hi]),
+                                   (int64_t)(w ? n[hi] : 1));
+            }
+        }
+    }
+    for (int q = 0; q < 3; ++q) {
+        const int64_t cols = (int64_t)(run_table_bytes(vol, q, 2) / 16);
+        hipLaunchKernelGGL(k_run_ends, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, s, h, q,
+                           (double2*)(base + run_table_offset(vol, q, 2)), cols);
+    }
+    return check_launch("volume_pack crossing tables");
 }
 
 int32_t drr_volume_pack(const float* src, void* packed, const drr_volume_desc* vol, void* stream)
@@ -202,6 +262,7 @@ int32_t drr_volume_pack(const float* src, void* packed, const drr_volume_desc* v
         st = check_launch("volume_pack");
         if (st) return st;
     }
+    if (has_run_tables(*vol)) return pack_run_tables(src, packed, *vol, as_stream(stream));
     return DRR_OK;
 }
 

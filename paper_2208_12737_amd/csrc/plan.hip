@@ -33,7 +33,9 @@
 
 namespace drr {
 
-constexpr int kPlanModes = 4;   // groups: kImage, kCount, kJac, kNcc (see group_mode)
+constexpr int kPlanModes = 4;   // kImage, kCount, kJac, kNcc (see group_mode)
+// groups: the modes on volumes without crossing tables, then on those with
+constexpr int kGroups = 2 * kPlanModes;
 constexpr int kXcds = 8;
 constexpr int kRing = 4;        // item tables in flight
 constexpr size_t kMaxGraphsPerSlot = 16;   // captured launches kept per item table
@@ -51,23 +53,24 @@ struct PlanItem {
     float* grad;
     double* partials;     // [tiles][kNccSums]
     int32_t tiles_x;
-    int32_t tile_begin;   // first tile of this item within its group
-    int32_t tiles;        // tiles of this item
+    int32_t tiles_y;
+    int32_t tile_begin;   // first workgroup tile of this item within its group
     int32_t pad;
 };
 
-// Render mode of group g (groups are indexed 0..kPlanModes-1).
+// Render mode of group g.
 __host__ __device__ constexpr int group_mode(int g)
 {
-    return g == 0 ? kImage : (g == 1 ? kCount : (g == 2 ? kJac : kNcc));
+    const int m = g % kPlanModes;
+    return m == 0 ? kImage : (m == 1 ? kCount : (m == 2 ? kJac : kNcc));
 }
 
 struct PlanHeader {
-    int32_t first[kPlanModes];     // first item of each group
-    int32_t count[kPlanModes];     // items per group
-    int32_t tiles[kPlanModes];     // tiles per group
-    int32_t uniform[kPlanModes];   // tiles per item when all items of the group
-                                   // have the same count, else 0
+    int32_t first[kGroups];     // first item of each group
+    int32_t count[kGroups];     // items per group
+    int32_t tiles[kGroups];     // workgroup tiles per group
+    int32_t uniform[kGroups];   // workgroup tiles per item when all items of the group
+                                // have the same count, else 0
 };
 // the item table follows the header: keep its doubles aligned
 static_assert(sizeof(PlanHeader) % 16 == 0, "PlanHeader size must keep items aligned");
@@ -76,10 +79,12 @@ struct Slot {
     PlanHeader* h_header = nullptr;   // pinned: header followed by items
     PlanItem* h_items = nullptr;
     char* d_block = nullptr;          // device copy of header + items
-    int32_t* d_counters = nullptr;    // [kPlanModes][kXcds]
+    int32_t* d_counters = nullptr;    // [kGroups][kXcds]
     hipEvent_t done = nullptr;
     bool used = false;
-    std::map<std::vector<int>, hipGraphExec_t> graphs;   // by mode mask (+ flat grids)
+    int pair[kGroups] = {};           // tiles a workgroup of each staged group (1 or 2)
+    int wgs[kGroups] = {};            // workgroups a CU of each staged group
+    std::map<std::vector<int>, hipGraphExec_t> graphs;   // by mode mask (+ grids)
 };
 
 // ------------------------------------------------------------------ kernels
@@ -120,15 +125,34 @@ __device__ inline int next_tile(int32_t* counters, int total, int xcd, int* scan
     return -1;
 }
 
-template <int TW, int WX, int WY, int MODE>
-__global__ __launch_bounds__(64 * WX * WY) void render_persistent(const char* __restrict__ block,
+// Outputs of the workgroup whose first tile is (tx, ty * G) of an item.
+template <int MODE, int G>
+__device__ inline TileOut item_out(const PlanItem& it, int tx, int ty)
+{
+    TileOut o;
+    o.image = it.image;
+    o.jac = it.jac;
+    o.counts = it.counts;
+    o.aux = MODE == kNcc ? it.target : nullptr;
+    o.partial = nullptr;
+    if (MODE == kNcc) {
+        o.partial = it.partials + ((int64_t)ty * G * it.tiles_x + tx) * kNccSums;
+        o.partial_step = (int64_t)it.tiles_x * kNccSums;
+        o.groups = min(G, it.tiles_y - ty * G);
+    }
+    return o;
+}
+
+// (G tiles a workgroup, one below the other)
+template <int TW, int WX, int WY, int MODE, typename RUNS, int G = 1>
+__global__ __launch_bounds__(64 * WX * WY * G, run_waves<RUNS>()) void render_persistent(const char* __restrict__ block,
                                                                   int32_t* counters, int group)
 {
     using S = TileShape<TW, WX, WY>;
     __shared__ int s_tile;
-    __shared__ double lds[MODE == kNcc ? kNccSums * WX * WY : 1];
+    __shared__ double lds[MODE == kNcc ? kNccSums * WX * WY * G : 1];
     static_assert(sizeof(lds) + sizeof(s_tile) <=
-                      16 + tile_sum_lds_bytes(MODE == kNcc ? kNccSums : 0, WX * WY),
+                      16 + tile_sum_lds_bytes(MODE == kNcc ? kNccSums : 0, WX * WY * G),
                   "static LDS budget");
     const PlanHeader* hdr = (const PlanHeader*)block;
     const PlanItem* items = (const PlanItem*)(block + sizeof(PlanHeader));
@@ -147,16 +171,11 @@ __global__ __launch_bounds__(64 * WX * WY) void render_persistent(const char* __
         const PlanItem& it = items[first + item_of_tile(hdr, items, group, t)];
         const int local = t - it.tile_begin;
         const int ty = local / it.tiles_x, tx = local % it.tiles_x;
-        TileOut o;
-        o.image = it.image;
-        o.jac = it.jac;
-        o.counts = it.counts;
-        o.aux = MODE == kNcc ? it.target : nullptr;
-        o.partial = MODE == kNcc ? it.partials + (int64_t)local * kNccSums : nullptr;
+        const TileOut o = item_out<MODE, G>(it, tx, ty);
         // (lean in the Jacobian modes: the loop over tiles and the item
         // fields would otherwise push them past 128 VGPRs, below four waves
         // per SIMD)
-        render_tile<TW, WX, WY, MODE, full_depth<MODE>(), ModeTraits<MODE>::jac>(
+        render_tile<TW, WX, WY, MODE, full_depth<MODE>(), RUNS, ModeTraits<MODE>::jac, G>(
             it.vol, it.det, it.pose, tx, ty, o, lds);
     }
     (void)sizeof(S);
@@ -165,12 +184,12 @@ __global__ __launch_bounds__(64 * WX * WY) void render_persistent(const char* __
 // Flat strategy: one workgroup per tile (grid = the group's tile count), the
 // hardware dispatcher as the queue, with the XCD-aware ordering of the
 // direct launches.  No atomics; the grid size is fixed per execute.
-template <int TW, int WX, int WY, int MODE>
-__global__ __launch_bounds__(64 * WX * WY) void render_plan_flat(const char* __restrict__ block,
+template <int TW, int WX, int WY, int MODE, typename RUNS, int G = 1>
+__global__ __launch_bounds__(64 * WX * WY * G, run_waves<RUNS>()) void render_plan_flat(const char* __restrict__ block,
                                                                  int group)
 {
-    __shared__ double lds[MODE == kNcc ? kNccSums * WX * WY : 1];
-    static_assert(sizeof(lds) <= 16 + tile_sum_lds_bytes(MODE == kNcc ? kNccSums : 0, WX * WY),
+    __shared__ double lds[MODE == kNcc ? kNccSums * WX * WY * G : 1];
+    static_assert(sizeof(lds) <= 16 + tile_sum_lds_bytes(MODE == kNcc ? kNccSums : 0, WX * WY * G),
                   "static LDS budget");
     const PlanHeader* hdr = (const PlanHeader*)block;
     const PlanItem* items = (const PlanItem*)(block + sizeof(PlanHeader));
@@ -178,15 +197,10 @@ __global__ __launch_bounds__(64 * WX * WY) void render_plan_flat(const char* __r
     const PlanItem& it = items[hdr->first[group] + item_of_tile(hdr, items, group, t)];
     const int local = t - it.tile_begin;
     const int ty = local / it.tiles_x, tx = local % it.tiles_x;
-    TileOut o;
-    o.image = it.image;
-    o.jac = it.jac;
-    o.counts = it.counts;
-    o.aux = MODE == kNcc ? it.target : nullptr;
-    o.partial = MODE == kNcc ? it.partials + (int64_t)local * kNccSums : nullptr;
+    const TileOut o = item_out<MODE, G>(it, tx, ty);
     // the flat grid serves small groups under the default strategy: the deep
     // pipeline keeps a lone wave's gathers in flight
-    render_tile<TW, WX, WY, MODE, kDeepDepth>(it.vol, it.det, it.pose, tx, ty, o, lds);
+    render_tile<TW, WX, WY, MODE, kDeepDepth, RUNS, false, G>(it.vol, it.det, it.pose, tx, ty, o, lds);
 }
 
 // Loss and pose gradient of every objective item: workgroup i reduces the
@@ -198,7 +212,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_plan_ncc_finalize(
     const PlanHeader* hdr = (const PlanHeader*)block;
     const PlanItem* items = (const PlanItem*)(block + sizeof(PlanHeader));
     const PlanItem& it = items[hdr->first[group] + (int)blockIdx.x];
-    sum_tile_partials<kNccSums>(it.partials, it.tiles, lds);
+    sum_tile_partials<kNccSums>(it.partials, it.tiles_x * it.tiles_y, lds);
     ncc_from_sums(lds, (double)it.det.H * (double)it.det.W, it.loss, it.grad);
 }
 
@@ -206,63 +220,100 @@ __global__ __launch_bounds__(kReduceThreads) void k_plan_ncc_finalize(
 
 typedef void (*PersistentFn)(const char*, int32_t*, int);
 
-template <int MODE>
+// With crossing tables the 16 x 16-pixel tiles of codes 0 and 4 are both of 8
+// x 8-pixel waves, as those of the direct launches.
+template <typename RUNS>
+static int wave_code(int code)
+{
+    return !std::is_void<RUNS>::value && code == 4 ? 0 : code;
+}
+
+template <int MODE, typename RUNS>
 static PersistentFn persistent_fn(int code)
 {
-    switch (code) {
-    case 0: return render_persistent<8, 2, 2, MODE>;
-    case 1: return render_persistent<8, 1, 1, MODE>;
-    case 2: return render_persistent<8, 1, 4, MODE>;
-    case 3: return render_persistent<16, 1, 4, MODE>;
-    case 4: return render_persistent<4, 4, 1, MODE>;
-    case 5: return render_persistent<8, 4, 1, MODE>;
-    case 6: return render_persistent<4, 1, 4, MODE>;
-    case 7: return render_persistent<2, 2, 2, MODE>;
-    default: return render_persistent<1, 4, 1, MODE>;
+    switch (wave_code<RUNS>(code)) {
+    case 0: return render_persistent<8, 2, 2, MODE, RUNS>;
+    case 1: return render_persistent<8, 1, 1, MODE, RUNS>;
+    case 2: return render_persistent<8, 1, 4, MODE, RUNS>;
+    case 3: return render_persistent<16, 1, 4, MODE, RUNS>;
+    case 4: return render_persistent<4, 4, 1, MODE, void>;
+    case 5: return render_persistent<8, 4, 1, MODE, RUNS>;
+    case 6: return render_persistent<4, 1, 4, MODE, RUNS>;
+    case 7: return render_persistent<2, 2, 2, MODE, RUNS>;
+    default: return render_persistent<1, 4, 1, MODE, RUNS>;
     }
 }
 
-static PersistentFn kernel_for(int group, int code)
+template <typename RUNS>
+static PersistentFn persistent_for(int group, int code)
 {
     switch (group_mode(group)) {
-    case kImage: return persistent_fn<kImage>(code);
-    case kCount: return persistent_fn<kCount>(code);
-    case kJac: return persistent_fn<kJac>(code);
-    default: return persistent_fn<kNcc>(code);
+    case kImage: return persistent_fn<kImage, RUNS>(code);
+    case kCount: return persistent_fn<kCount, RUNS>(code);
+    case kJac: return persistent_fn<kJac, RUNS>(code);
+    default: return persistent_fn<kNcc, RUNS>(code);
     }
+}
+
+static PersistentFn kernel_for(int group, int code, int pair)
+{
+    if (pair == 2) {
+        switch (group_mode(group)) {
+        case kImage: return render_persistent<8, 2, 2, kImage, RunFull, 2>;
+        case kCount: return render_persistent<8, 2, 2, kCount, RunFull, 2>;
+        case kJac: return render_persistent<8, 2, 2, kJac, RunFull, 2>;
+        default: return render_persistent<8, 2, 2, kNcc, RunFull, 2>;
+        }
+    }
+    return group >= kPlanModes ? persistent_for<RunFull>(group, code)
+                               : persistent_for<void>(group, code);
 }
 
 typedef void (*FlatFn)(const char*, int);
 
-template <int MODE>
+template <int MODE, typename RUNS>
 static FlatFn flat_fn(int code)
 {
-    switch (code) {
-    case 0: return render_plan_flat<8, 2, 2, MODE>;
-    case 1: return render_plan_flat<8, 1, 1, MODE>;
-    case 2: return render_plan_flat<8, 1, 4, MODE>;
-    case 3: return render_plan_flat<16, 1, 4, MODE>;
-    case 4: return render_plan_flat<4, 4, 1, MODE>;
-    case 5: return render_plan_flat<8, 4, 1, MODE>;
-    case 6: return render_plan_flat<4, 1, 4, MODE>;
-    case 7: return render_plan_flat<2, 2, 2, MODE>;
-    default: return render_plan_flat<1, 4, 1, MODE>;
+    switch (wave_code<RUNS>(code)) {
+    case 0: return render_plan_flat<8, 2, 2, MODE, RUNS>;
+    case 1: return render_plan_flat<8, 1, 1, MODE, RUNS>;
+    case 2: return render_plan_flat<8, 1, 4, MODE, RUNS>;
+    case 3: return render_plan_flat<16, 1, 4, MODE, RUNS>;
+    case 4: return render_plan_flat<4, 4, 1, MODE, void>;
+    case 5: return render_plan_flat<8, 4, 1, MODE, RUNS>;
+    case 6: return render_plan_flat<4, 1, 4, MODE, RUNS>;
+    case 7: return render_plan_flat<2, 2, 2, MODE, RUNS>;
+    default: return render_plan_flat<1, 4, 1, MODE, RUNS>;
     }
 }
 
-static FlatFn flat_kernel_for(int group, int code)
+template <typename RUNS>
+static FlatFn flat_for(int group, int code)
 {
     switch (group_mode(group)) {
-    case kImage: return flat_fn<kImage>(code);
-    case kCount: return flat_fn<kCount>(code);
-    case kJac: return flat_fn<kJac>(code);
-    default: return flat_fn<kNcc>(code);
+    case kImage: return flat_fn<kImage, RUNS>(code);
+    case kCount: return flat_fn<kCount, RUNS>(code);
+    case kJac: return flat_fn<kJac, RUNS>(code);
+    default: return flat_fn<kNcc, RUNS>(code);
     }
+}
+
+static FlatFn flat_kernel_for(int group, int code, int pair)
+{
+    if (pair == 2) {
+        switch (group_mode(group)) {
+        case kImage: return render_plan_flat<8, 2, 2, kImage, RunFull, 2>;
+        case kCount: return render_plan_flat<8, 2, 2, kCount, RunFull, 2>;
+        case kJac: return render_plan_flat<8, 2, 2, kJac, RunFull, 2>;
+        default: return render_plan_flat<8, 2, 2, kNcc, RunFull, 2>;
+        }
+    }
+    return group >= kPlanModes ? flat_for<RunFull>(group, code) : flat_for<void>(group, code);
 }
 
 enum Strategy { kPersistent = 0, kFlat = 1, kAuto = 2 };
 
-// Group of an item: 0 image, 1 image + counts, 2 image + Jacobian,
+// Mode group of an item: 0 image, 1 image + counts, 2 image + Jacobian,
 // 3 objective.
 static int group_of_flags(int32_t flags)
 {
@@ -274,18 +325,20 @@ static int group_of_flags(int32_t flags)
 
 // Upper bound of the static LDS of group g's plan kernels: the tile index
 // and the block-sum buffer of the objective group.
-static size_t plan_static_lds(int g, const ShapeInfo& sh)
+static size_t plan_static_lds(int g, const ShapeInfo& sh, int pair)
 {
-    return 16 + tile_sum_lds_bytes(group_mode(g) == kNcc ? kNccSums : 0, sh.wx * sh.wy);
+    return 16 + tile_sum_lds_bytes(group_mode(g) == kNcc ? kNccSums : 0, sh.wx * sh.wy * pair);
 }
 
 // Tiles of a detector for launch shape `code`.
-static int64_t tiles_for(const drr_detector_desc& d, int code, int* tiles_x)
+static int64_t tiles_for(const drr_detector_desc& d, int code, int* tiles_x,
+                         int* tiles_y = nullptr)
 {
     const ShapeInfo& sh = kShapes[code];
     const int pxw = sh.tw * sh.wx, pxh = (64 / sh.tw) * sh.wy;
     const int tx = (d.width + pxw - 1) / pxw, ty = (d.height + pxh - 1) / pxh;
     if (tiles_x) *tiles_x = tx;
+    if (tiles_y) *tiles_y = ty;
     return (int64_t)tx * ty;
 }
 
@@ -300,7 +353,8 @@ struct drr_plan {
     int strategy = 0;          // kPersistent, kFlat or kAuto
     int tile_code = 0;
     int wg_per_cu = 0;         // requested workgroups per CU (0 = occupancy limit)
-    int grid[kPlanModes] = {0, 0, 0, 0};   // persistent grid per group
+    bool wg_chosen = false;    // by the caller or the autotuner
+    int grid[2][kGroups] = {}; // persistent grid per tiles a workgroup and group
     int num_cus = 0;
     bool use_graph = false;
     Slot slots[kRing];
@@ -319,18 +373,47 @@ static int32_t compute_grids(drr_plan* p)
 {
     const ShapeInfo& sh = kShapes[p->tile_code];
     const int threads = 64 * sh.wx * sh.wy;
-    for (int m = 0; m < kPlanModes; ++m) {
-        int occ = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &occ, (const void*)kernel_for(m, p->tile_code), threads, 0);
-        if (e != hipSuccess || occ < 1)
-            return fail(DRR_EHIP, "occupancy query failed: %s", hipGetErrorString(e));
-        int per = p->wg_per_cu > 0 && p->wg_per_cu < occ ? p->wg_per_cu : occ;
-        p->grid[m] = per * p->num_cus;
-        // whole multiples of the XCD count keep the XCD shares balanced
-        p->grid[m] = ((p->grid[m] + kXcds - 1) / kXcds) * kXcds;
+    for (int pair = 1; pair <= 2; ++pair) {
+        for (int m = 0; m < kGroups; ++m) {
+            int occ = 0;
+            if (pair == 2 && m < kPlanModes) continue;
+            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &occ, (const void*)kernel_for(m, p->tile_code, pair), threads * pair, 0);
+            if (e != hipSuccess || occ < 1)
+                return fail(DRR_EHIP, "occupancy query failed: %s", hipGetErrorString(e));
+            p->grid[pair - 1][m] = occ;
+        }
     }
     return DRR_OK;
+}
+
+// Tiles a workgroup and workgroups a CU for a group of items: two tiles on
+// the volumes whose tables bound the launch, given work for all CUs (see
+// run_big_tables; the smallest count of the group's volumes).
+static void choose_pair(const drr_plan* p, const drr_work_item* items, int n, int m, Slot& s)
+{
+    int64_t tiles = 0;
+    int big = 0;
+    for (int i = 0; i < n; ++i) {
+        const drr_volume_desc& v = p->vols[items[i].volume];
+        if (group_of_flags(items[i].flags) + (has_run_tables(v) ? kPlanModes : 0) != m) continue;
+        tiles += tiles_for(items[i].det, p->tile_code, nullptr);
+        const int wgs = run_big_tables(v, items[i].det);
+        if (wgs > 0) big = big == 0 || wgs < big ? wgs : big;
+    }
+    const bool two = m >= kPlanModes && (p->tile_code == 0 || p->tile_code == 4) && big > 0 &&
+                     tiles > 8ll * p->num_cus;
+    s.pair[m] = two ? 2 : 1;
+    s.wgs[m] = !two ? p->wg_per_cu : (p->wg_chosen ? (p->wg_per_cu + 1) / 2 : big);
+}
+
+// Workgroups of group m's persistent launch: a multiple of the XCD count
+// keeps the XCD shares balanced.
+static int persistent_grid(const drr_plan* p, const Slot& s, int m)
+{
+    const int occ = p->grid[s.pair[m] - 1][m];
+    const int per = s.wgs[m] > 0 && s.wgs[m] < occ ? s.wgs[m] : occ;
+    return ((per * p->num_cus + kXcds - 1) / kXcds) * kXcds;
 }
 
 // Fills slot `s` for the given items; returns the mode mask via *mask.
@@ -339,14 +422,16 @@ static int32_t stage_items(drr_plan* p, Slot& s, const drr_work_item* items, int
     PlanHeader* h = s.h_header;
     int pos = 0;
     *mask = 0;
-    for (int m = 0; m < kPlanModes; ++m) {
+    for (int m = 0; m < kGroups; ++m) {
         h->first[m] = pos;
         h->count[m] = 0;
         h->uniform[m] = 0;
         int64_t tiles = 0, per = -1;
+        choose_pair(p, items, n, m, s);
         for (int i = 0; i < n; ++i) {
             const drr_work_item& w = items[i];
-            if (group_of_flags(w.flags) != m) continue;
+            const bool runs = has_run_tables(p->vols[w.volume]);
+            if (group_of_flags(w.flags) + (runs ? kPlanModes : 0) != m) continue;
             PlanItem& it = s.h_items[pos++];
             it.vol = vol_args(p->packed[w.volume], p->vols[w.volume]);
             it.det = det_args(w.det);
@@ -358,8 +443,8 @@ static int32_t stage_items(drr_plan* p, Slot& s, const drr_work_item* items, int
             it.loss = w.loss;
             it.grad = w.grad;
             it.partials = w.partials;
-            const int64_t t = tiles_for(w.det, p->tile_code, &it.tiles_x);
-            it.tiles = (int32_t)t;
+            tiles_for(w.det, p->tile_code, &it.tiles_x, &it.tiles_y);
+            const int64_t t = (int64_t)it.tiles_x * ((it.tiles_y + s.pair[m] - 1) / s.pair[m]);
             it.tile_begin = (int32_t)tiles;
             tiles += t;
             per = per == -1 || per == t ? t : 0;
@@ -376,18 +461,21 @@ static int32_t stage_items(drr_plan* p, Slot& s, const drr_work_item* items, int
 // The objective group's losses and gradients, after its tiles are rendered.
 static int32_t enqueue_finalize(Slot& s, int mask, hipStream_t st)
 {
-    constexpr int g = 3;
-    if (!(mask & (1 << g))) return DRR_OK;
-    hipLaunchKernelGGL(k_plan_ncc_finalize, dim3(s.h_header->count[g]), dim3(kReduceThreads), 0,
-                       st, (const char*)s.d_block, g);
-    return check_launch("plan objective finalize");
+    for (int g = 0; g < kGroups; ++g) {
+        if (group_mode(g) != kNcc || !(mask & (1 << g))) continue;
+        hipLaunchKernelGGL(k_plan_ncc_finalize, dim3(s.h_header->count[g]), dim3(kReduceThreads),
+                           0, st, (const char*)s.d_block, g);
+        const int32_t rc = check_launch("plan objective finalize");
+        if (rc) return rc;
+    }
+    return DRR_OK;
 }
 
 // Strategy of group m in the staged execute.
 static int group_strategy(const drr_plan* p, const Slot& s, int m)
 {
     if (p->strategy != kAuto) return p->strategy;
-    return s.h_header->tiles[m] <= p->grid[m] ? kFlat : kPersistent;
+    return s.h_header->tiles[m] <= persistent_grid(p, s, m) ? kFlat : kPersistent;
 }
 
 static int32_t enqueue_kernels(drr_plan* p, Slot& s, int mask, hipStream_t st)
@@ -396,23 +484,25 @@ static int32_t enqueue_kernels(drr_plan* p, Slot& s, int mask, hipStream_t st)
     const int threads = 64 * sh.wx * sh.wy;
     int32_t rc;
     bool counters_reset = false;
-    for (int m = 0; m < kPlanModes; ++m) {
+    for (int m = 0; m < kGroups; ++m) {
         if (!(mask & (1 << m))) continue;
         if (group_strategy(p, s, m) == kFlat) {
-            const size_t lds = occupancy_lds(p->wg_per_cu, plan_static_lds(m, sh));
-            hipLaunchKernelGGL(flat_kernel_for(m, p->tile_code), dim3(s.h_header->tiles[m]),
-                               dim3(threads), lds, st, (const char*)s.d_block, m);
+            const size_t lds = occupancy_lds(s.wgs[m], plan_static_lds(m, sh, s.pair[m]));
+            hipLaunchKernelGGL(flat_kernel_for(m, p->tile_code, s.pair[m]),
+                               dim3(s.h_header->tiles[m]), dim3(threads * s.pair[m]), lds, st,
+                               (const char*)s.d_block, m);
             if ((rc = check_launch("plan flat kernel"))) return rc;
             continue;
         }
         if (!counters_reset) {
             hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, st, s.d_counters,
-                               kPlanModes * kXcds);
+                               kGroups * kXcds);
             if ((rc = check_launch("plan counter reset"))) return rc;
             counters_reset = true;
         }
-        hipLaunchKernelGGL(kernel_for(m, p->tile_code), dim3(p->grid[m]), dim3(threads), 0, st,
-                           (const char*)s.d_block, s.d_counters, m);
+        hipLaunchKernelGGL(kernel_for(m, p->tile_code, s.pair[m]), dim3(persistent_grid(p, s, m)),
+                           dim3(threads * s.pair[m]), 0, st, (const char*)s.d_block, s.d_counters,
+                           m);
         if ((rc = check_launch("plan persistent kernel"))) return rc;
     }
     return enqueue_finalize(s, mask, st);
@@ -440,12 +530,13 @@ static int32_t execute_locked(drr_plan* p, const drr_work_item* items, int n, hi
     if (e != hipSuccess) return fail(DRR_EHIP, "plan table copy: %s", hipGetErrorString(e));
     if (p->use_graph && st != nullptr) {
         // what the captured launches depend on: groups present, the
-        // finalize grid, and each group's strategy with its flat grid size
-        std::vector<int> key = {mask, s.h_header->count[3]};
-        for (int m = 0; m < kPlanModes; ++m) {
+        // finalize grids, and each group's strategy with its flat grid size
+        std::vector<int> key = {mask, s.h_header->count[3], s.h_header->count[3 + kPlanModes]};
+        for (int m = 0; m < kGroups; ++m) {
             const int g = group_strategy(p, s, m);
             key.push_back(g);
             key.push_back(g == kFlat ? s.h_header->tiles[m] : 0);
+            key.push_back(s.pair[m] * 256 + s.wgs[m]);
         }
         auto found = s.graphs.find(key);
         if (found == s.graphs.end()) {
@@ -596,6 +687,7 @@ static int32_t autotune(drr_plan* p, const drr_work_item* items, int n, hipStrea
                         const char* cache)
 {
     const std::string key = tune_key(p, items, n);
+    p->wg_chosen = true;
     int strategy = 0, code = 0, wpc = 0;
     if (cache_lookup(cache, key, &strategy, &code, &wpc)) {
         p->strategy = strategy;
@@ -607,7 +699,7 @@ static int32_t autotune(drr_plan* p, const drr_work_item* items, int n, hipStrea
     int best_code = 0, best_wpc = 0, best_strategy = kPersistent;
     // resident workgroups per CU: the register limit, or fewer (less cache
     // pressure from concurrent rays)
-    const int wpcs[] = {0, 3, 4, 5, 6};
+    const int wpcs[] = {0, 2, 3, 4, 5, 6};
     for (int strat = kPersistent; strat <= kFlat; ++strat) {
         for (int c = 0; c < kNumShapes; ++c) {
             for (int w : wpcs) {
@@ -682,7 +774,7 @@ int32_t drr_plan_create(const drr_plan_desc* desc, const drr_work_item* tune_ite
     for (Slot& s : p->slots) {
         if (hipHostMalloc((void**)&s.h_header, tb, hipHostMallocDefault) != hipSuccess ||
             hipMalloc((void**)&s.d_block, tb) != hipSuccess ||
-            hipMalloc((void**)&s.d_counters, kPlanModes * kXcds * sizeof(int32_t)) !=
+            hipMalloc((void**)&s.d_counters, kGroups * kXcds * sizeof(int32_t)) !=
                 hipSuccess ||
             hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess) {
             free_plan(p);
@@ -705,6 +797,7 @@ int32_t drr_plan_create(const drr_plan_desc* desc, const drr_work_item* tune_ite
         p->strategy = desc->strategy >= 0 ? desc->strategy : kAuto;
         p->tile_code = desc->tile_code >= 0 ? desc->tile_code : 4;
         p->wg_per_cu = desc->wg_per_cu >= 0 ? desc->wg_per_cu : 4;
+        p->wg_chosen = desc->wg_per_cu >= 0;
     }
     int32_t rc = compute_grids(p);
     if (rc == DRR_OK && desc->autotune) {

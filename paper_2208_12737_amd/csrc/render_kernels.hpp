@@ -21,7 +21,10 @@
 //   kL2Loss   image (optional) + per-tile sum of (I-T)^2
 #pragma once
 
+#include <type_traits>
+
 #include "launch_budget.hpp"
+#include "runs.hpp"
 #include "siddon.hpp"
 
 namespace drr {
@@ -65,7 +68,9 @@ struct TileOut {
     float* jac;        // [H][W][7]
     int32_t* counts;   // [H][W]
     const float* aux;  // [H][W]
-    double* partial;   // nsum doubles
+    double* partial;   // nsum doubles (of the workgroup's first tile)
+    int64_t partial_step = 0;   // to its next tile's
+    int groups = 1;             // its tiles inside the detector
 };
 
 template <int TW, int WX, int WY>
@@ -76,9 +81,12 @@ struct TileShape {
     static constexpr int threads = 64 * WX * WY;
 };
 
-// Fixed-order workgroup reduction of NS per-lane values into out[0..NS).
-template <int NS, int NWAVES>
-__device__ inline void block_sums(double (&vals)[NS], double* lds, double* out)
+// Fixed-order reduction of NS per-lane values over each group of NWAVES
+// waves of the workgroup (one tile each): group g's sums go to
+// out[g * step .. + NS) if g < groups.
+template <int NS, int NWAVES, int G>
+__device__ inline void block_sums(double (&vals)[NS], double* lds, double* out, int64_t step = 0,
+                                  int groups = 1)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -87,42 +95,21 @@ __device__ inline void block_sums(double (&vals)[NS], double* lds, double* out)
         if (lane == 0) lds[wave * NS + k] = s;
     }
     __syncthreads();
-    if ((int)threadIdx.x < NS) {
+    const int g = (int)threadIdx.x / (64 * NWAVES), i = (int)threadIdx.x % (64 * NWAVES);
+    if (i < NS && g < groups) {
         double acc = 0.0;
-        for (int wv = 0; wv < NWAVES; ++wv) acc += lds[wv * NS + threadIdx.x];
-        out[threadIdx.x] = acc;
+        for (int wv = 0; wv < NWAVES; ++wv) acc += lds[(g * NWAVES + wv) * NS + i];
+        out[g * step + i] = acc;
     }
     __syncthreads();
 }
 
-// Always inlined: an out-of-line call (the plan kernels have two call sites
-// per instance) passes the volume and detector fields in vector registers and
-// turns their uses into per-lane loads.
-// LEAN: for kernels that carry more state of their own (the persistent plan
-// kernels, short of scalar registers), the pose's trigonometry is evaluated
-// per lane and rebuilt in the Jacobian tail rather than kept through the
-// loop, and the Jacobian loop is the masked one only (see trace()); the
-// results are the same bits.
-template <int TW, int WX, int WY, int MODE, int DEPTH, bool LEAN = false>
-__device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
-                                            const float* __restrict__ pose, int tx, int ty,
-                                            const TileOut& o, double* lds)
+// The ray's sums from the voxel copies, by the plane merge.
+template <int MODE, int DEPTH, bool LEAN, bool GATHER = true>
+__device__ __forceinline__ RayAcc merge_ray(const VolArgs& V, const Mat3& R, bool inside,
+                                            const double s[3], const double d[3])
 {
-    using S = TileShape<TW, WX, WY>;
     using T = ModeTraits<MODE>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wx = wave % WX, wy = wave / WX;
-    const int w = (tx * WX + wx) * TW + lane % TW;
-    const int h = (ty * WY + wy) * S::th + lane / TW;
-    const bool inside = (w < D.W) && (h < D.H);
-
-    const PoseTrig q = LEAN ? pose_trig_per_lane(pose) : pose_trig(pose);
-    const Mat3 R = rotation(q.ct, q.st, q.cp, q.sp, q.cg, q.sg, -1);
-    const double u = ((double)w + 0.5 - 0.5 * (double)D.W) * (double)D.dx + D.ou;
-    const double v = ((double)h + 0.5 - 0.5 * (double)D.H) * (double)D.dy + D.ov;
-    double s[3], d[3];
-    ray_of(q, R, u, v, s, d);
-
     // Copy of the volume for this pose: by the principal axis of its
     // central ray (the direction of -R e_x), the same for the whole tile.
     int principal = 0;
@@ -143,7 +130,7 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
 
     RayAcc r;
     r.sum = 0.0;
-    r.a0 = r.a1 = r.a2 = r.b0 = r.b1 = r.b2 = 0.0f;
+    r.a0 = r.a1 = r.a2 = r.b0 = r.b1 = r.b2 = 0.0;
     r.nseg = 0;
     r.valid = true;
     // Axis whose Jacobian sums are derived from the identities: the
@@ -155,7 +142,7 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
         __builtin_amdgcn_readfirstlane((e0 >= e1 && e0 >= e2) ? 0 : (e1 >= e2 ? 1 : 2));
     if (inside) {
         if (!T::jac)
-            r = trace<false, T::count, 0, DEPTH>(V, rsrc, pitch, s, d);
+            r = trace<false, T::count, 0, DEPTH, true, GATHER>(V, rsrc, pitch, s, d);
         else if (derived == 0)
             r = trace<T::jac, T::count, 0, DEPTH, !LEAN>(V, rsrc, pitch, s, d);
         else if (derived == 1)
@@ -163,8 +150,76 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
         else
             r = trace<T::jac, T::count, 2, DEPTH, !LEAN>(V, rsrc, pitch, s, d);
     }
+    return r;
+}
 
-    const double L = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+// Always inlined: an out-of-line call (the plan kernels have two call sites
+// per instance) passes the volume and detector fields in vector registers and
+// turns their uses into per-lane loads.
+// A workgroup renders G tiles one below the other (tx, ty: of the first, ty in
+// units of G tiles); WX x WY are the waves of one tile.
+// RUNS: for volumes with crossing tables (used unless they are marked as
+// too coarse for the volume), how they are read: RunFull or RunFew, void for
+// volumes without; DEPTH is that of the merge.
+// LEAN: for kernels that carry more state of their own (the persistent plan
+// kernels, short of scalar registers), the pose's trigonometry is evaluated
+// per lane and rebuilt in the Jacobian tail rather than kept through the
+// loop, and the Jacobian loop is the masked one only (see trace()); the
+// results are the same bits.
+template <int TW, int WX, int WY, int MODE, int DEPTH, typename RUNS, bool LEAN = false, int G = 1>
+__device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
+                                            const float* __restrict__ pose, int tx, int ty,
+                                            const TileOut& o, double* lds)
+{
+    using S = TileShape<TW, WX, WY>;
+    using T = ModeTraits<MODE>;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wx = wave % WX, wy = wave / WX;
+    const int w = (tx * WX + wx) * TW + lane % TW;
+    const int h = (ty * (WY * G) + wy) * S::th + lane / TW;
+    const bool inside = (w < D.W) && (h < D.H);
+
+    const PoseTrig q = LEAN ? pose_trig_per_lane(pose) : pose_trig(pose);
+    const double u = ((double)w + 0.5 - 0.5 * (double)D.W) * (double)D.dx + D.ou;
+    const double v = ((double)h + 0.5 - 0.5 * (double)D.H) * (double)D.dy + D.ov;
+
+    RayAcc r;
+    double L;
+    auto merge = [&](auto gather) {
+        const Mat3 R = rotation(q.ct, q.st, q.cp, q.sp, q.cg, q.sg, -1);
+        double s[3], d[3];
+        ray_of(q, R, u, v, s, d);
+        L = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        return merge_ray<MODE, DEPTH, LEAN, decltype(gather)::value>(V, R, inside, s, d);
+    };
+    if constexpr (!std::is_void<RUNS>::value) {
+        if (run_tables_usable(V)) {
+            // (the opaque copies keep the compiler from holding the ray, or
+            // the rotation, from one call to the next)
+            auto ray = [&](double s[3], double d[3]) {
+                const PoseTrig p = LEAN ? pose_trig_per_lane(launder(pose)) : launder_trig(q);
+                const Mat3 R = rotation(p.ct, p.st, p.cp, p.sp, p.cg, p.sg, -1);
+                const int w_ = launder_int(w), h_ = launder_int(h);
+                const double u_ = ((double)w_ + 0.5 - 0.5 * (double)D.W) * (double)D.dx + D.ou;
+                const double v_ = ((double)h_ + 0.5 - 0.5 * (double)D.H) * (double)D.dy + D.ov;
+                ray_of(p, R, u_, v_, s, d);
+            };
+            // the pose's central ray runs along -R e_x
+            const double axis[3] = {q.ct * q.cp, q.st * q.cp, q.sp};
+            r = trace_runs<T::jac, RUNS>(V, inside, ray, run_direction(axis, V.inv_spacing, -1), L);
+            // the count is that of the merge's segments (no voxel is read)
+            if constexpr (T::count) {
+                const double length = L;
+                r.nseg = merge(std::false_type{}).nseg;
+                L = length;
+            }
+        } else {
+            r = merge(std::true_type{});
+        }
+    } else {
+        r = merge(std::true_type{});
+    }
+
     const float E = r.valid ? (float)(L * r.sum) : __builtin_nanf("");
     const int64_t pix = (int64_t)h * D.W + w;
 
@@ -199,7 +254,7 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
         double vals[7];
 #pragma unroll
         for (int j = 0; j < 7; ++j) vals[j] = inside ? (double)g * (double)J[j] : 0.0;
-        block_sums<7, WX * WY>(vals, lds, o.partial);
+        block_sums<7, WX * WY, G>(vals, lds, o.partial, o.partial_step, o.groups);
     }
     if (MODE == kNcc) {
         const double I = inside ? (double)E : 0.0;
@@ -217,13 +272,13 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
             vals[12 + j] = Tv * Jj;
             vals[19 + j] = I * Jj;
         }
-        block_sums<kNccSums, WX * WY>(vals, lds, o.partial);
+        block_sums<kNccSums, WX * WY, G>(vals, lds, o.partial, o.partial_step, o.groups);
     }
     if (MODE == kNccLoss) {
         const double I = inside ? (double)E : 0.0;
         const double Tv = inside ? (double)o.aux[pix] : 0.0;
         double vals[5] = {I, I * I, Tv, Tv * Tv, I * Tv};
-        block_sums<5, WX * WY>(vals, lds, o.partial);
+        block_sums<5, WX * WY, G>(vals, lds, o.partial, o.partial_step, o.groups);
     }
     if constexpr (MODE == kL2 || MODE == kL2Loss) {
         const double r_ = inside ? (double)E - (double)o.aux[pix] : 0.0;
@@ -233,7 +288,7 @@ __device__ __forceinline__ void render_tile(const VolArgs& V, const DetArgs& D,
 #pragma unroll
             for (int j = 0; j < 7; ++j) vals[1 + j] = inside ? r_ * (double)J[j] : 0.0;
         }
-        block_sums<T::nsum, WX * WY>(vals, lds, o.partial);
+        block_sums<T::nsum, WX * WY, G>(vals, lds, o.partial, o.partial_step, o.groups);
     }
 }
 
@@ -257,18 +312,28 @@ __device__ inline void pose_tile(uint32_t bid, uint32_t total, uint32_t tiles, i
     }
 }
 
-// Flat launch: grid = wg_per_pose * n_poses workgroups, XCD-aware ordering.
-template <int TW, int WX, int WY, int MODE, int DEPTH>
-__global__ __launch_bounds__(64 * WX * WY) void render_flat(
-    VolArgs V, DetArgs D, const float* __restrict__ poses, int tiles_x, int wg_per_pose,
+// Waves per SIMD that a kernel's registers must allow: four where the launch
+// has that many (128 registers; the Jacobian modes keep some 50 bytes of
+// set-up in memory for it), any number otherwise.
+template <typename RUNS>
+constexpr int run_waves()
+{
+    return std::is_same<RUNS, RunFull>::value ? 4 : 1;
+}
+
+// Flat launch: grid = workgroups per pose * n_poses, XCD-aware ordering; a
+// workgroup takes G of a pose's tiles_x * tiles_y tiles.
+template <int TW, int WX, int WY, int MODE, int DEPTH, typename RUNS, int G = 1>
+__global__ __launch_bounds__(64 * WX * WY * G, run_waves<RUNS>()) void render_flat(
+    VolArgs V, DetArgs D, const float* __restrict__ poses, int tiles_x, int tiles_y,
     float* image, float* jac, int32_t* counts, const float* aux, int64_t aux_stride,
     double* partials)
 {
     using T = ModeTraits<MODE>;
-    __shared__ double lds[(T::nsum > 0 ? T::nsum : 1) * WX * WY];
-    static_assert(sizeof(lds) == tile_sum_lds_bytes(T::nsum, WX * WY), "static LDS budget");
+    __shared__ double lds[(T::nsum > 0 ? T::nsum : 1) * WX * WY * G];
+    static_assert(sizeof(lds) == tile_sum_lds_bytes(T::nsum, WX * WY * G), "static LDS budget");
     int b, t;
-    pose_tile(blockIdx.x, gridDim.x, (uint32_t)wg_per_pose, &b, &t);
+    pose_tile(blockIdx.x, gridDim.x, (uint32_t)(tiles_x * ((tiles_y + G - 1) / G)), &b, &t);
     const int ty = t / tiles_x, tx = t % tiles_x;
     const int64_t hw = (int64_t)D.H * D.W;
     TileOut o;
@@ -276,8 +341,14 @@ __global__ __launch_bounds__(64 * WX * WY) void render_flat(
     o.jac = jac ? jac + b * hw * (MODE == kJacDet ? 4 : 7) : nullptr;
     o.counts = counts ? counts + b * hw : nullptr;
     o.aux = aux ? aux + b * aux_stride : nullptr;
-    o.partial = T::nsum > 0 ? partials + ((int64_t)b * wg_per_pose + t) * T::nsum : nullptr;
-    render_tile<TW, WX, WY, MODE, DEPTH>(V, D, poses + 7 * b, tx, ty, o, lds);
+    o.partial = nullptr;
+    if (T::nsum > 0) {
+        const int64_t tile = ((int64_t)b * tiles_y + ty * G) * tiles_x + tx;
+        o.partial = partials + tile * T::nsum;
+        o.partial_step = (int64_t)tiles_x * T::nsum;
+        o.groups = min(G, tiles_y - ty * G);
+    }
+    render_tile<TW, WX, WY, MODE, DEPTH, RUNS, false, G>(V, D, poses + 7 * b, tx, ty, o, lds);
 }
 
 }  // namespace drr

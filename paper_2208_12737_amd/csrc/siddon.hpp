@@ -54,7 +54,29 @@ struct VolArgs {
     uint32_t copy_bytes;
     int32_t pitch[3][3];
     int32_t copy_for[3];
+    // crossing tables (run: their header, NULL when the volume has none):
+    // byte offsets, for runs along axis q, of the crossings of the lower and
+    // of the higher of the other two axes, and of the columns' end sums
+    const char* run;
+    uint64_t run_off[3][3];
+    double inv_spacing[3];
 };
+
+// Start of the crossing tables.  Filled when the volume is packed: the
+// quantum of the runs along each axis, the largest jump (its bits; FP64
+// values >= 0 order like integers), the sum of |V|, and whether the tables
+// are accurate enough to be used.
+struct RunHeader {
+    double quantum[3];
+    unsigned long long most[3];
+    double sum_abs;
+    int32_t use;
+};
+constexpr uint64_t kRunHeaderBytes = 256;
+
+// Entries of a table row beyond the voxels of q: one before the grid and two
+// after it (a rounded position may lie just outside).
+constexpr int kRunPad = 3;
 
 struct DetArgs {
     double dx, dy;   // pitch
@@ -171,7 +193,7 @@ __device__ inline void ray_of(const PoseTrig& q, const Mat3& R, double u, double
 // to would multiply the error by millions.
 struct RayAcc {
     double sum;
-    float a0, a1, a2, b0, b1, b2;
+    double a0, a1, a2, b0, b1, b2;
     int32_t nseg;
     bool valid;  // false: non-finite geometry (result NaN)
 };
@@ -202,7 +224,9 @@ __device__ inline double min_nn(double a, double b)
 // whose rays all fold their exit (see `clip`); without it every wave takes
 // the masked loop, which gives the same bits at some 2 VALU instructions
 // more per step and a few registers fewer.
-template <bool JAC, bool COUNT, int DERIVED, int DEPTH, bool FOLDED_LOOP = true>
+// GATHER: read the voxels (without it only the segments are counted).
+template <bool JAC, bool COUNT, int DERIVED, int DEPTH, bool FOLDED_LOOP = true,
+          bool GATHER = true>
 __device__ inline RayAcc trace(const VolArgs& V, const __amdgpu_buffer_rsrc_t& rsrc,
                                const int32_t pitch[3], const double s[3], const double d[3])
 {
@@ -212,7 +236,7 @@ __device__ inline RayAcc trace(const VolArgs& V, const __amdgpu_buffer_rsrc_t& r
     constexpr int derived = DERIVED;
     RayAcc r;
     r.sum = 0.0;
-    r.a0 = r.a1 = r.a2 = r.b0 = r.b1 = r.b2 = 0.0f;
+    r.a0 = r.a1 = r.a2 = r.b0 = r.b1 = r.b2 = 0.0;
     r.nseg = 0;
     r.valid = true;
 
@@ -387,7 +411,7 @@ __device__ inline RayAcc trace(const VolArgs& V, const __amdgpu_buffer_rsrc_t& r
             ad = fma(bd ? 0x1p-7 : 0.0, dd, ad);                                 \
         }                                                                        \
         off += b1 ? s1 : (b2 ? s2 : sd);                                         \
-        vn = ld(rsrc, off);                                                      \
+        vn = GATHER ? ld(rsrc, off) : 0.0f;                                      \
         /* keep the gather where it is: the scheduler would otherwise sink  */ \
         /* it towards its use and shorten the distance the pipeline buys    */ \
         __builtin_amdgcn_sched_barrier(0);                                       \
@@ -463,7 +487,7 @@ __device__ inline RayAcc trace(const VolArgs& V, const __amdgpu_buffer_rsrc_t& r
             constexpr int NR = DEPTH + 2;
             float v[NR];
             double a[NR], p[NR], q[NR];   // p, q: step factors of axes e1, e2
-            v[0] = ld(rsrc, off);
+            v[0] = GATHER ? ld(rsrc, off) : 0.0f;
             a[0] = amin;
 #pragma unroll
             for (int k = 0; k < NR; ++k) {
@@ -504,7 +528,7 @@ __device__ inline RayAcc trace(const VolArgs& V, const __amdgpu_buffer_rsrc_t& r
         constexpr int NR = DEPTH + 1;
         float v[NR];
         double a[NR], p[NR], q[NR];
-        v[0] = ld(rsrc, off);
+        v[0] = GATHER ? ld(rsrc, off) : 0.0f;
         a[0] = amin;
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
@@ -689,6 +713,32 @@ __device__ inline T* launder(T* p)
     return p;
 }
 
+__device__ inline int launder_int(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// The same for the wave-uniform values of a pose (they stay scalar).
+__device__ inline double launder_scalar(double x)
+{
+    int lo = __double2loint(x), hi = __double2hiint(x);
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return __hiloint2double(hi, lo);
+}
+
+__device__ inline PoseTrig launder_trig(const PoseTrig& q)
+{
+    PoseTrig p = q;
+    p.ct = launder_scalar(q.ct);
+    p.st = launder_scalar(q.st);
+    p.cp = launder_scalar(q.cp);
+    p.sp = launder_scalar(q.sp);
+    p.cg = launder_scalar(q.cg);
+    p.sg = launder_scalar(q.sg);
+    return p;
+}
+
 // The descriptor must live in scalar registers.  Where the volume arguments
 // were read from memory (plan item tables) the compiler cannot prove them
 // wave-uniform and would wrap every gather in a loop over distinct
@@ -699,6 +749,18 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const VolArgs& V, int copy)
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)addr);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(addr >> 32));
     const int nrec = __builtin_amdgcn_readfirstlane((int)V.copy_bytes);
+    const char* base = (const char*)(((uint64_t)hi << 32) | lo);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nrec, (int)kBufferDword3);
+}
+
+// Descriptor of `bytes` bytes at offset `off` of the crossing tables.
+__device__ inline __amdgpu_buffer_rsrc_t make_run_rsrc(const VolArgs& V, uint64_t off,
+                                                       uint32_t bytes)
+{
+    const uint64_t addr = (uint64_t)V.run + off;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)addr);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(addr >> 32));
+    const int nrec = __builtin_amdgcn_readfirstlane((int)bytes);
     const char* base = (const char*)(((uint64_t)hi << 32) | lo);
     return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, nrec, (int)kBufferDword3);
 }

@@ -89,6 +89,13 @@ class Detector:
 
 
 LAYOUTS = {"input": _lib.DRR_LAYOUT_INPUT, "per_axis": _lib.DRR_LAYOUT_PER_AXIS}
+COPIES = {"input": 1, "per_axis": 3}
+
+
+def _copies_bytes(shape, layout: str) -> int:
+    """Bytes of the zero-bordered voxel copies."""
+    nx, ny, nz = shape
+    return 4 * COPIES[layout] * (nx + 2) * (ny + 2) * (nz + 2)
 
 
 class Volume:
@@ -97,8 +104,10 @@ class Volume:
     data: float32 tensor of shape (nx, ny, nz) (C-order, any device);
     spacing: voxel size in mm; origin: position of plane 0 per axis (default
     centres the grid on the world origin); layout: "per_axis" (three copies,
-    one per principal ray axis, fastest) or "input" (one copy).  Renders are
-    bitwise identical for both layouts.
+    one per principal ray axis) or "input" (one copy).  Behind the copies the
+    volume holds the crossing tables that renders are made from (some 24 bytes
+    a voxel, left out where they would not fit their 32-bit offsets).  Renders
+    are bitwise identical for both layouts.
     """
 
     def __init__(self, data: torch.Tensor, spacing, origin=None, device=None,
@@ -116,23 +125,33 @@ class Volume:
         if layout not in LAYOUTS:
             raise ValueError(f"layout must be one of {sorted(LAYOUTS)}")
         self.layout = layout
-        self.desc = _lib.volume_desc(self.shape, self.spacing, self.origin, LAYOUTS[layout])
-        nbytes = _lib.load().drr_volume_packed_bytes(ctypes.byref(self.desc))
-        if nbytes == 0:
+        self.desc = _lib.volume_desc(self.shape, self.spacing, self.origin,
+                                     LAYOUTS[layout] | _lib.DRR_LAYOUT_CROSSINGS)
+        total = _lib.load().drr_volume_packed_bytes(ctypes.byref(self.desc))
+        if total == 0:
             _lib.check("drr_volume_packed_bytes", _lib.DRR_EINVAL)
-        self.packed = torch.empty(nbytes // 4, dtype=torch.float32, device=device)
+        self._store = torch.empty(total, dtype=torch.uint8, device=device)
+        # the copies; the tables follow them in the same allocation
+        self.packed = self._store[:_copies_bytes(self.shape, layout)].view(torch.float32)
         _lib.call("drr_volume_pack", src.data_ptr(), self.packed.data_ptr(),
                   ctypes.byref(self.desc), _stream())
         self.device = device
 
     @property
     def nbytes(self) -> int:
+        """Bytes of the voxel copies."""
         return self.packed.numel() * 4
+
+    @property
+    def total_bytes(self) -> int:
+        """Bytes of the copies and the crossing tables."""
+        return self._store.numel()
 
 
 def choose_layout(data: torch.Tensor, spacing, det: "Detector", poses: torch.Tensor, origin=None,
                   device=None, max_bytes: int | None = None, reps: int = 5):
-    """Pack `data` in each layout whose packed size fits `max_bytes`, time the
+    """Pack `data` in each layout whose copies fit `max_bytes` (the crossing
+    tables, the same for every layout, come on top), time the
     forward render of `poses` on `det` from each (median of `reps` launches
     after two warm-ups, HIP events on the current stream), and return the
     Volume in the fastest layout and the times {layout: ms}.  The layouts give
@@ -144,11 +163,7 @@ def choose_layout(data: torch.Tensor, spacing, det: "Detector", poses: torch.Ten
     best = None
     for name in ("per_axis", "input"):
         if max_bytes is not None:
-            shape = tuple(int(v) for v in data.shape)
-            org = origin if origin is not None else tuple(-0.5 * n * float(s)
-                                                          for n, s in zip(shape, spacing))
-            desc = _lib.volume_desc(shape, spacing, org, LAYOUTS[name])
-            if _lib.load().drr_volume_packed_bytes(ctypes.byref(desc)) > max_bytes:
+            if _copies_bytes(tuple(int(v) for v in data.shape), name) > max_bytes:
                 continue
         vol = Volume(data, spacing, origin, device=device, layout=name)
         for _ in range(2):
