@@ -222,17 +222,20 @@ static int32_t pack_run_tables(const float* src, void* packed, const drr_volume_
     char* base = (char*)packed + run_header_offset(vol);
     RunHeader* h = (RunHeader*)base;
     hipLaunchKernelGGL(k_run_clear, dim3(1), dim3(64), 0, s, h);
-    for (int pass = 0; pass < 3; ++pass) {
-        if (pass == 2) hipLaunchKernelGGL(k_run_quanta, dim3(1), dim3(64), 0, s, h, n[0], n[1], n[2]);
+    for (int fill = 0; fill < 2; ++fill) {
+        if (fill) hipLaunchKernelGGL(k_run_quanta, dim3(1), dim3(64), 0, s, h, n[0], n[1], n[2]);
         for (int q = 0; q < 3; ++q) {
             double2* ends = (double2*)(base + run_table_offset(vol, q, 2));
             const int lo = q == 0 ? 1 : 0, hi = q == 2 ? 1 : 2;
-            for (int w = 0; w < (pass == 0 ? 1 : 2); ++w) {
+            for (int w = 0; w < 2; ++w) {
                 // strips along the axis whose planes the table holds
                 const int a = w ? hi : lo, b = w ? lo : hi;
-                auto scan = pass == 0 ? k_run_scan<0> : (pass == 1 ? k_run_scan<1> : k_run_scan<2>);
-                hipLaunchKernelGGL(scan, dim3(n[b], (n[a] + kRunCols) / kRunCols), dim3(256), 0, s,
-                                   src, h, q, ends, w == 0,
+                const bool along_b = b == 2;   // the contiguous axis of the source
+                auto scan = along_b ? (fill ? k_run_scan<true, true> : k_run_scan<false, true>)
+                                    : (fill ? k_run_scan<true, false> : k_run_scan<false, false>);
+                const dim3 grid = along_b ? dim3((n[b] + 63) / 64, n[a] / 4 + 1)
+                                          : dim3((n[b] + 3) / 4, n[a] / kRunStrip + 1);
+                hipLaunchKernelGGL(scan, grid, dim3(256), 0, s, src, h, q, w == 0, ends,
                                    (int*)(base + run_table_offset(vol, q, w)), n[a], n[b], n[q],
                                    pitch[a], pitch[b], pitch[q], (int64_t)(w ? 1 : n[hi]),
                                    (int64_t)(w ? n[hi] : 1));
@@ -253,12 +256,15 @@ int32_t drr_volume_pack(const float* src, void* packed, const drr_volume_desc* v
     if (st) return st;
     if (!src || !packed) return fail(DRR_EINVAL, "volume_pack: NULL pointer");
     const uint64_t total = copy_elems(*vol);
-    const unsigned blocks = (unsigned)((total + 255) / 256);
     for (int q = 0; q < num_copies(*vol); ++q) {
         const CopyOrder o = copy_order(*vol, q);
-        hipLaunchKernelGGL(k_pack, dim3(blocks), dim3(256), 0, as_stream(stream), src,
+        const int f = o.axis[2] == 2 ? 1 : o.axis[2];
+        const int nf = f == 0 ? vol->nx : vol->ny, ng = f == 0 ? vol->ny : vol->nx;
+        const uint64_t blocks = (uint64_t)((vol->nz + 1) / kPackTile + 1) *
+                                (uint64_t)((nf + 1) / kPackTile + 1) * (uint64_t)(ng + 2);
+        hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, as_stream(stream), src,
                            (float*)packed + q * total, vol->nx, vol->ny, vol->nz, o.axis[0],
-                           o.axis[1], o.axis[2], total);
+                           o.axis[1], o.axis[2]);
         st = check_launch("volume_pack");
         if (st) return st;
     }

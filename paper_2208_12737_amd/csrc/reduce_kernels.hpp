@@ -172,23 +172,56 @@ __global__ void k_momentum(float* __restrict__ poses, float* __restrict__ vel,
     poses[i] = poses[i] - rate[i] * v;
 }
 
-// Copies a C-order volume into one zero-bordered copy whose memory order is
-// (o0 slowest, o1, o2 fastest) over the padded dims P.
-__global__ void k_pack(const float* __restrict__ src, float* __restrict__ dst, int nx, int ny,
-                       int nz, int o0, int o1, int o2, uint64_t total)
+// Copies a C-order volume into one zero-bordered copy of the padded dims P
+// whose memory order is o0 slowest, o1, o2 fastest: tiles of 32 x 32 over o2
+// and z, read along z and written along o2 through LDS (o2 = z: as they are),
+// one padded index of the third axis a workgroup.  Bound by its reads and
+// writes: 101..126 us a copy of the 512 x 512 x 133 CT (279 MB), 205 us as one
+// thread a voxel that reads across z.
+constexpr int kPackTile = 32;
+
+__global__ __launch_bounds__(256) void k_pack(const float* __restrict__ src,
+                                              float* __restrict__ dst, int nx, int ny, int nz,
+                                              int o0, int o1, int o2)
 {
-    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total) return;
-    const uint64_t P[3] = {(uint64_t)nx + 2, (uint64_t)ny + 2, (uint64_t)nz + 2};
-    uint64_t idx[3];
-    idx[o2] = e % P[o2];
-    idx[o1] = (e / P[o2]) % P[o1];
-    idx[o0] = e / (P[o2] * P[o1]);
-    const int i = (int)idx[0], j = (int)idx[1], k = (int)idx[2];
-    float v = 0.0f;
-    if (i >= 1 && i <= nx && j >= 1 && j <= ny && k >= 1 && k <= nz)
-        v = src[((uint64_t)(i - 1) * ny + (j - 1)) * nz + (k - 1)];
-    dst[e] = v;
+    __shared__ float tile[kPackTile][kPackTile + 1];
+    const int n[3] = {nx, ny, nz};
+    const int f = o2 == 2 ? 1 : o2;             // the axis of the tile beside z
+    const int g = f == 0 ? 1 : 0;               // the third
+    const int nf = f == 0 ? nx : ny;
+    const uint32_t tz = (uint32_t)(nz + 1) / kPackTile + 1, tf = (uint32_t)(nf + 1) / kPackTile + 1;
+    const int z0 = (int)(blockIdx.x % tz) * kPackTile, f0 = (int)(blockIdx.x / tz % tf) * kPackTile;
+    const int ig = (int)(blockIdx.x / tz / tf), ng = g == 0 ? nx : ny;
+    const int lane = threadIdx.x % kPackTile, line = threadIdx.x / kPackTile;
+    const int64_t sf = f == 0 ? (int64_t)ny * nz : nz, sg = g == 0 ? (int64_t)ny * nz : nz;
+    // pitches of the copy
+    int64_t pitch_z = 0, pitch_f = 0, pitch_g = 0, at = 1;
+    for (int k = 2; k >= 0; --k) {
+        const int axis = k == 2 ? o2 : (k == 1 ? o1 : o0);
+        if (axis == 2) pitch_z = at;
+        else if (axis == f) pitch_f = at;
+        else pitch_g = at;
+        at *= (axis == 0 ? n[0] : (axis == 1 ? n[1] : n[2])) + 2;
+    }
+    // padded indices; voxel i of an axis is at i + 1
+    auto voxel = [&](int pf, int pz) {
+        const bool in = pf >= 1 && pf <= nf && pz >= 1 && pz <= nz && ig >= 1 && ig <= ng;
+        return in ? src[(pf - 1) * sf + (ig - 1) * sg + (pz - 1)] : 0.0f;
+    };
+    if (o2 == 2) {
+        for (int r = line; r < kPackTile; r += 8) {
+            const int pf = f0 + r, pz = z0 + lane;
+            if (pf < nf + 2 && pz < nz + 2) dst[pf * pitch_f + ig * pitch_g + pz] = voxel(pf, pz);
+        }
+        return;
+    }
+    for (int r = line; r < kPackTile; r += 8) tile[r][lane] = voxel(f0 + r, z0 + lane);
+    __syncthreads();
+    for (int r = line; r < kPackTile; r += 8) {
+        const int pf = f0 + lane, pz = z0 + r;
+        if (pf < nf + 2 && pz < nz + 2)
+            dst[pf * pitch_f + ig * pitch_g + pz * pitch_z] = tile[lane][r];
+    }
 }
 
 // ------------------------------------------------------------------ crossing tables
@@ -221,95 +254,141 @@ __global__ void k_run_quanta(RunHeader* h, int nx, int ny, int nz)
         const double most = __longlong_as_double((long long)h->most[q]);
         const double quantum = most / kRunMost;
         h->quantum[q] = quantum;
-        use = use && quantum > 0.0 && quantum <= 0x1p-26 * mean * (double)n[q];
+        use = use && quantum > 0.0 && isfinite(quantum) &&
+              quantum <= 0x1p-26 * mean * (double)n[q];
     }
     h->use = use ? 1 : 0;
 }
 
-// Running sums along axis q of a strip of columns, neighbours along axis a,
-// at one column c of axis b.  A workgroup takes the columns k0 - 1 .. k0 + 63
-// (those outside the grid sum to 0), stages 32 voxels of each through LDS and
-// lets one lane a column add them up in order; the jumps across the planes
-// k0 .. k0 + 63 are differences of neighbouring lanes' sums.
-//   PASS 0  ends[column] = {-total / 2, total / 2}, and the sum of |V|
-//   PASS 1  the largest jump
-//   PASS 2  the table; the end sums in quanta
-// Sums run from -total / 2, rounded to quanta (PASS 2): entries of row (k, c)
-// are the jumps before voxel i - 1 of q, i = 0 .. n + 2, held at both ends.
-// Set-up once a volume: 2.0 ms for the 512 x 512 x 133 CT.
-constexpr int kRunCols = 64, kRunStage = 32;
+// Running sums along axis q and their jumps across the planes of axis a.
+// Lanes are neighbours along whichever axis the source is contiguous in:
+//   ALONG_B  along b: a lane adds up both columns of its plane
+//   else     along a (or each along its own row of q): a lane adds up one
+//            column, and the jumps of 63 planes are differences of
+//            neighbouring lanes' sums
+//   MEASURE  (!FILL) the largest jump of sums taken from the middle of the
+//            columns' totals (from the extremes and the end of the jumps of
+//            the plain sums); with `first`, the totals and, for q = 0, the
+//            sum of |V|
+//   FILL     the table, of sums from -total / 2 rounded to quanta: entries i
+//            = 0 .. n + 2 of row (k, c) are the jumps before voxel i - 1 of q,
+//            held at both ends; with `first`, the sums at the ends
+// Columns outside the grid sum to 0.  Bound by the latency of its reads (some
+// 1500 waves), so 16 voxels are read ahead of the 16 being summed; rows are
+// written four entries at a time.  A table of the 512 x 512 x 133 CT measures
+// in 88..119 us and fills in 149..216 us (139 MB read, as much written).
+// Lanes always along a: 350 and 490 us with b the contiguous axis, all twelve
+// passes 2.9 ms for 1.7.
+constexpr int kRunStrip = 63, kRunAhead = 16;
+typedef float run_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int run_i4 __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int PASS>
+template <bool FILL, bool ALONG_B>
 __global__ __launch_bounds__(256) void k_run_scan(const float* __restrict__ src, RunHeader* h,
-                                                  int q, double2* ends, bool keep_end,
+                                                  int q, bool first, double2* ends,
                                                   int* __restrict__ table, int na, int nb, int nq,
-                                                  int64_t sa, int64_t sb, int64_t sq,
-                                                  int64_t ea, int64_t eb)
+                                                  int64_t sa, int64_t sb, int64_t sq, int64_t ea,
+                                                  int64_t eb)
 {
-    __shared__ float vox[kRunCols + 1][kRunStage + 1];
-    __shared__ double sum[kRunCols + 1][kRunStage + 1];
-    const int tid = threadIdx.x, c = blockIdx.x, k0 = (int)blockIdx.y * kRunCols;
-    // column j of the strip is cell k0 - 1 + j of axis a
-    auto cell = [&](int j) { return k0 - 1 + j; };
-    const bool column = tid <= kRunCols && cell(tid) >= 0 && cell(tid) < na;
-    // (a NaN stays)
-    auto larger = [](double a, double b) { return (b > a || b != b) ? b : a; };
-    double inv = 0.0, acc = 0.0, absolute = 0.0, most = 0.0;
-    if (PASS == 2 && h->use == 0) return;   // the tables are not read
-    if (PASS == 2) inv = 1.0 / h->quantum[q];
-    const double2* end = ends + (int64_t)cell(tid) * ea + (int64_t)c * eb;
-    if (PASS > 0 && column) acc = end->x;
-    // (fetching along whichever of a and q is contiguous in the source)
-    const bool along_q = sq == 1;
-    for (int m0 = 0; m0 <= nq; m0 += kRunStage) {
-        for (int e = tid; e < (kRunCols + 1) * kRunStage; e += 256) {
-            const int j = along_q ? e / kRunStage : e % (kRunCols + 1);
-            const int m = along_q ? e % kRunStage : e / (kRunCols + 1);
-            const int a = cell(j), i = m0 + m;
-            vox[j][m] = (a >= 0 && a < na && i < nq)
-                            ? src[(int64_t)a * sa + (int64_t)c * sb + (int64_t)i * sq]
-                            : 0.0f;
+    if (FILL && h->use == 0) return;   // the tables are not read
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // the lane's column `cell` (above its plane) at c; four neighbouring
+    // waves a workgroup
+    int c, cell;
+    bool plane;
+    if (ALONG_B) {
+        c = (int)blockIdx.x * 64 + lane;
+        cell = (int)blockIdx.y * 4 + wave;
+        plane = c < nb && cell <= na;
+    } else {
+        c = (int)blockIdx.x * 4 + wave;
+        if (c >= nb) return;
+        cell = (int)blockIdx.y * kRunStrip - 1 + lane;
+        plane = lane >= 1 && cell <= na;
+    }
+    const bool column = c < nb && cell >= 0 && cell < na;
+    const bool under = ALONG_B && plane && cell > 0;   // the column below, added up as well
+    const float* in = src + (column ? (int64_t)cell * sa + (int64_t)c * sb : 0);
+    const float* in2 = src + (under ? (int64_t)(cell - 1) * sa + (int64_t)c * sb : 0);
+    double2* end = ends + (column ? (int64_t)cell * ea + (int64_t)c * eb : 0);
+    int* row = table + (plane ? ((int64_t)cell * nb + c) * (nq + kRunPad) : 0);
+    const double inv = FILL ? 1.0 / h->quantum[q] : 0.0;
+    double acc = FILL && column ? end->x : 0.0;
+    double acc2 = FILL && under ? ends[(int64_t)(cell - 1) * ea + (int64_t)c * eb].x : 0.0;
+    double absolute = 0.0, lo = 0.0, hi = 0.0;
+    bool nan = false;
+    auto below = [&](double above, double x2) { return ALONG_B ? x2 : __shfl_up(above, 1, 64); };
+    float now[kRunAhead], next[kRunAhead], now2[kRunAhead], next2[kRunAhead];
+    auto fetch = [&](float* v, const float* p, bool on, int i0) {
+        if (!ALONG_B && sq == 1 && i0 + kRunAhead <= nq) {
+#pragma unroll
+            for (int u = 0; u < kRunAhead; u += 4) {
+                const run_f4 x = on ? *(const run_f4*)(p + i0 + u) : run_f4{0.0f, 0.0f, 0.0f, 0.0f};
+                v[u] = x.x, v[u + 1] = x.y, v[u + 2] = x.z, v[u + 3] = x.w;
+            }
+            return;
         }
-        __syncthreads();
-        if (tid <= kRunCols) {
-            for (int m = 0; m < kRunStage; ++m) {
-                sum[tid][m] = PASS == 2 ? rint(acc * inv) : acc;
-                const double x = (double)vox[tid][m];
-                if (column) acc += x;
-                if (PASS == 0 && column && tid > 0) absolute += fabs(x);
+#pragma unroll
+        for (int u = 0; u < kRunAhead; ++u)
+            v[u] = on && i0 + u < nq ? p[(int64_t)(i0 + u) * sq] : 0.0f;
+    };
+    fetch(now, in, column, 0);
+    if (ALONG_B) fetch(now2, in2, under, 0);
+    int held[4] = {0, 0, 0, 0};
+    for (int i0 = 0; i0 <= nq; i0 += kRunAhead) {
+        fetch(next, in, column, i0 + kRunAhead);
+        if (ALONG_B) fetch(next2, in2, under, i0 + kRunAhead);
+#pragma unroll
+        for (int u = 0; u < kRunAhead; ++u) {
+            const int i = i0 + u;
+            const double s = FILL ? rint(acc * inv) : acc;
+            const double jump = below(s, FILL ? rint(acc2 * inv) : acc2) - s;
+            if (FILL) {
+                const int j = (int)jump;
+                if (plane && i == 0) row[0] = j;
+                held[u & 3] = j;
+                // entries i - 2 .. i + 1 of the row
+                if ((u & 3) == 3 && plane && i <= nq)
+                    *(run_i4*)(row + i - 2) = run_i4{held[0], held[1], held[2], held[3]};
+                else if (plane && i <= nq && i + 3 - (u & 3) > nq)
+                    row[i + 1] = j;   // the last, incomplete four
+                if (plane && i == nq) row[nq + 2] = j;
+            } else if (i <= nq) {
+                lo = fmin(lo, jump);
+                hi = fmax(hi, jump);
+                nan = nan || jump != jump;
+            }
+            if (i < nq) {
+                acc += (double)now[u];
+                if (ALONG_B) acc2 += (double)now2[u];
+                if (!FILL) absolute += fabs((double)now[u]);
             }
         }
-        __syncthreads();
-        if (PASS > 0) {
-            for (int e = tid; e < kRunCols * kRunStage; e += 256) {
-                const int j = e / kRunStage, m = e % kRunStage;
-                const int k = k0 + j, i = m0 + m;
-                if (k > na || i > nq) continue;
-                const double jump = sum[j][m] - sum[j + 1][m];
-                if (PASS == 1) most = larger(most, fabs(jump));
-                if (PASS == 2) {
-                    int* row = table + ((int64_t)k * nb + c) * (nq + kRunPad);
-                    row[i + 1] = (int)jump;
-                    if (i == 0) row[0] = (int)jump;
-                    if (i == nq) row[nq + 2] = (int)jump;
-                }
-            }
-            __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kRunAhead; ++u) {
+            now[u] = next[u];
+            if (ALONG_B) now2[u] = next2[u];
         }
     }
-    double2* out = ends + (int64_t)cell(tid) * ea + (int64_t)c * eb;
-    if (PASS == 0) {
-        if (column && tid > 0) *out = make_double2(-0.5 * acc, 0.5 * acc);
-        const double s = wave_sum(absolute);
-        if ((tid & 63) == 0) atomicAdd(&h->sum_abs, s);
+    const bool owned = column && (ALONG_B || lane > 0);
+    if (FILL) {
+        // (only .x is read by other waves)
+        if (first && owned) end->y = acc;
+        return;
     }
-    if (PASS == 1) {
-        // the sum at the end as the tables' scans reach it (only .x is read
-        // by other workgroups)
-        if (keep_end && column && tid > 0) out->y = acc;
-        for (int o = 32; o >= 1; o >>= 1) most = larger(most, __shfl_xor(most, o, 64));
-        if ((tid & 63) == 0)
-            atomicMax(&h->most[q], (unsigned long long)__double_as_longlong(fabs(most)));
+    if (first && owned) *end = make_double2(-0.5 * acc, 0.5 * acc);
+    const double last = below(acc, acc2) - acc;
+    double most = plane ? fmax(hi - 0.5 * last, 0.5 * last - lo) : 0.0;
+    if (plane && (nan || most != most)) most = __builtin_nan("");
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double x = __shfl_xor(most, o, 64);
+        most = (x > most || x != x) ? x : most;   // a NaN stays
+    }
+    if (lane == 0)
+        atomicMax(&h->most[q], (unsigned long long)__double_as_longlong(fabs(most)));
+    if (first && q == 0) {
+        const double s = wave_sum(owned ? absolute : 0.0);
+        if (lane == 0) atomicAdd(&h->sum_abs, s);
     }
 }
 
