@@ -106,8 +106,11 @@ static int32_t launch_flat(const void* packed, const drr_volume_desc& vol,
         const int wgs = run_big_tables(vol, det);
         if (wgs == 0 || blocks <= 8ull * cus)
             return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull>, 1, set >= 0 ? set : 4);
-        return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull, 2>, 2,
-                      set >= 0 ? (set + 1) / 2 : wgs);
+        const int pairs = set >= 0 ? (set + 1) / 2 : wgs;
+        if constexpr (ModeTraits<MODE>::jac)
+            if (pairs == 1)
+                return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunWide, 2>, 2, pairs);
+        return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull, 2>, 2, pairs);
     }
     if constexpr (MODE == kImage || MODE == kCount) {
         // per-pixel results that do not depend on the launch shape: a launch

@@ -255,14 +255,17 @@ static PersistentFn persistent_for(int group, int code)
     }
 }
 
-static PersistentFn kernel_for(int group, int code, int pair)
+// wide: pairs of tiles, one pair a CU (RunWide in the Jacobian modes).
+static PersistentFn kernel_for(int group, int code, int pair, bool wide = false)
 {
     if (pair == 2) {
         switch (group_mode(group)) {
         case kImage: return render_persistent<8, 2, 2, kImage, RunFull, 2>;
         case kCount: return render_persistent<8, 2, 2, kCount, RunFull, 2>;
-        case kJac: return render_persistent<8, 2, 2, kJac, RunFull, 2>;
-        default: return render_persistent<8, 2, 2, kNcc, RunFull, 2>;
+        case kJac:
+            return wide ? render_persistent<8, 2, 2, kJac, RunWide, 2> : render_persistent<8, 2, 2, kJac, RunFull, 2>;
+        default:
+            return wide ? render_persistent<8, 2, 2, kNcc, RunWide, 2> : render_persistent<8, 2, 2, kNcc, RunFull, 2>;
         }
     }
     return group >= kPlanModes ? persistent_for<RunFull>(group, code)
@@ -298,14 +301,16 @@ static FlatFn flat_for(int group, int code)
     }
 }
 
-static FlatFn flat_kernel_for(int group, int code, int pair)
+static FlatFn flat_kernel_for(int group, int code, int pair, bool wide = false)
 {
     if (pair == 2) {
         switch (group_mode(group)) {
         case kImage: return render_plan_flat<8, 2, 2, kImage, RunFull, 2>;
         case kCount: return render_plan_flat<8, 2, 2, kCount, RunFull, 2>;
-        case kJac: return render_plan_flat<8, 2, 2, kJac, RunFull, 2>;
-        default: return render_plan_flat<8, 2, 2, kNcc, RunFull, 2>;
+        case kJac:
+            return wide ? render_plan_flat<8, 2, 2, kJac, RunWide, 2> : render_plan_flat<8, 2, 2, kJac, RunFull, 2>;
+        default:
+            return wide ? render_plan_flat<8, 2, 2, kNcc, RunWide, 2> : render_plan_flat<8, 2, 2, kNcc, RunFull, 2>;
         }
     }
     return group >= kPlanModes ? flat_for<RunFull>(group, code) : flat_for<void>(group, code);
@@ -486,9 +491,10 @@ static int32_t enqueue_kernels(drr_plan* p, Slot& s, int mask, hipStream_t st)
     bool counters_reset = false;
     for (int m = 0; m < kGroups; ++m) {
         if (!(mask & (1 << m))) continue;
+        const bool wide = s.pair[m] == 2 && s.wgs[m] == 1;
         if (group_strategy(p, s, m) == kFlat) {
             const size_t lds = occupancy_lds(s.wgs[m], plan_static_lds(m, sh, s.pair[m]));
-            hipLaunchKernelGGL(flat_kernel_for(m, p->tile_code, s.pair[m]),
+            hipLaunchKernelGGL(flat_kernel_for(m, p->tile_code, s.pair[m], wide),
                                dim3(s.h_header->tiles[m]), dim3(threads * s.pair[m]), lds, st,
                                (const char*)s.d_block, m);
             if ((rc = check_launch("plan flat kernel"))) return rc;
@@ -500,7 +506,8 @@ static int32_t enqueue_kernels(drr_plan* p, Slot& s, int mask, hipStream_t st)
             if ((rc = check_launch("plan counter reset"))) return rc;
             counters_reset = true;
         }
-        hipLaunchKernelGGL(kernel_for(m, p->tile_code, s.pair[m]), dim3(persistent_grid(p, s, m)),
+        hipLaunchKernelGGL(kernel_for(m, p->tile_code, s.pair[m], wide),
+                           dim3(persistent_grid(p, s, m)),
                            dim3(threads * s.pair[m]), 0, st, (const char*)s.d_block, s.d_counters,
                            m);
         if ((rc = check_launch("plan persistent kernel"))) return rc;

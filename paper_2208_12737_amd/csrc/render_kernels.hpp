@@ -159,8 +159,8 @@ __device__ __forceinline__ RayAcc merge_ray(const VolArgs& V, const Mat3& R, boo
 // A workgroup renders G tiles one below the other (tx, ty: of the first, ty in
 // units of G tiles); WX x WY are the waves of one tile.
 // RUNS: for volumes with crossing tables (used unless they are marked as
-// too coarse for the volume), how they are read: RunFull or RunFew, void for
-// volumes without; DEPTH is that of the merge.
+// too coarse for the volume), how they are read: RunFull, RunWide or RunFew,
+// void for volumes without; DEPTH is that of the merge.
 // LEAN: for kernels that carry more state of their own (the persistent plan
 // kernels, short of scalar registers), the pose's trigonometry is evaluated
 // per lane and rebuilt in the Jacobian tail rather than kept through the
@@ -313,12 +313,12 @@ __device__ inline void pose_tile(uint32_t bid, uint32_t total, uint32_t tiles, i
 }
 
 // Waves per SIMD that a kernel's registers must allow: four where the launch
-// has that many (128 registers; the Jacobian modes keep some 50 bytes of
-// set-up in memory for it), any number otherwise.
+// has that many (128 registers; the Jacobian modes keep some 180 bytes a lane
+// in memory for it), two where it has two, any number otherwise.
 template <typename RUNS>
 constexpr int run_waves()
 {
-    return std::is_same<RUNS, RunFull>::value ? 4 : 1;
+    return std::is_same<RUNS, RunFull>::value ? 4 : (std::is_same<RUNS, RunWide>::value ? 2 : 1);
 }
 
 // Flat launch: grid = workgroups per pose * n_poses, XCD-aware ordering; a

@@ -47,20 +47,26 @@ namespace drr {
 
 // Crossings whose table entries are read together, and whether the next
 // batch is read before the last is summed.
-//   kRunFull   launches that fill the GPU: eight at a time (an earlier build
+//   RunFull    launches that fill the GPU: eight at a time (an earlier build
 //              with all else equal: 4 at a time, pipelined, 256 poses of
 //              256 x 256 on the 512 x 512 x 133 CT level, the fused gradient
 //              of 64 poses 4% slower)
-//   kRunFew    launches of about a wave per SIMD, which have nothing else to
+//   RunWide    the same for the Jacobian modes where two waves a SIMD are
+//              resident anyway: 256 registers, nothing kept in memory (the
+//              fused gradient of 64 poses: 1.27 ms, 1.36 ms with 128
+//              registers; pipelined or with 16 at a time 1.28..1.30 ms; the
+//              modes without a Jacobian need no more than 128)
+//   RunFew     launches of about a wave per SIMD, which have nothing else to
 //              hide a read's latency: pairs of batches (one such DRR: 33 us
 //              with eight, 38 us with four, 39-48 us without the pipeline)
-//   kRunRare   a wave's second direction: small, for its registers
+//   RunRare    a wave's second direction: small, for its registers
 template <int UNROLL, bool PIPELINED>
 struct RunShape {
     static constexpr int unroll = UNROLL;
     static constexpr bool pipelined = PIPELINED;
 };
 using RunFull = RunShape<8, false>;
+struct RunWide : RunFull {};
 using RunFew = RunShape<8, true>;
 using RunRare = RunShape<2, true>;
 
