@@ -356,7 +356,7 @@ int32_t drr_render_backward(const drr_detector_desc* det, int32_t n_poses, const
     hipLaunchKernelGGL(k_jac_dot, dim3(chunks, n_poses), dim3(kReduceThreads), 0, s, jac,
                        grad_image, hw, chunks, (double*)workspace);
     if ((st = check_launch("jac_dot"))) return st;
-    hipLaunchKernelGGL(k_grad_finalize, dim3(n_poses), dim3(kReduceThreads), 0, s,
+    hipLaunchKernelGGL(k_grad_finalize, dim3(n_poses), dim3(final_threads<7>()), 0, s,
                        (const double*)workspace, chunks, grad_pose);
     return check_launch("grad_finalize");
 }
@@ -378,7 +378,7 @@ int32_t drr_render_backward_retrace(const void* packed, const drr_volume_desc* v
     st = launch_flat<kRetrace>(packed, *vol, *det, poses, n_poses, nullptr, nullptr, nullptr,
                                grad_image, hw, (double*)workspace, s);
     if (st) return st;
-    hipLaunchKernelGGL(k_grad_finalize, dim3(n_poses), dim3(kReduceThreads), 0, s,
+    hipLaunchKernelGGL(k_grad_finalize, dim3(n_poses), dim3(final_threads<7>()), 0, s,
                        (const double*)workspace, flat_grid(*det).wg_per_pose, grad_pose);
     return check_launch("grad_finalize");
 }
@@ -407,7 +407,7 @@ int32_t drr_ncc_forward(const float* image, const float* target, int64_t target_
                        target, target_stride, hw, chunks, (double*)workspace);
     int32_t st = check_launch("ncc_moments");
     if (st) return st;
-    hipLaunchKernelGGL(k_ncc_stats, dim3(n_poses), dim3(kReduceThreads), 0, s,
+    hipLaunchKernelGGL(k_ncc_stats, dim3(n_poses), dim3(final_threads<5>()), 0, s,
                        (const double*)workspace, chunks, (double)hw, stats, loss);
     return check_launch("ncc_stats");
 }
@@ -456,7 +456,7 @@ int32_t drr_render_ncc_grad(const void* packed, const drr_volume_desc* vol,
     st = launch_flat<kNcc>(packed, *vol, *det, poses, n_poses, image, nullptr, nullptr, target,
                            target_stride, (double*)workspace, s);
     if (st) return st;
-    hipLaunchKernelGGL(k_ncc_grad_finalize, dim3(n_poses), dim3(kReduceThreads), 0, s,
+    hipLaunchKernelGGL(k_ncc_grad_finalize, dim3(n_poses), dim3(final_threads<kNccSums>()), 0, s,
                        (const double*)workspace, flat_grid(*det).wg_per_pose, (double)hw, loss,
                        grad_pose);
     return check_launch("ncc_grad_finalize");
@@ -507,7 +507,7 @@ int32_t drr_render_ncc_loss(const void* packed, const drr_volume_desc* vol,
     st = launch_flat<kNccLoss>(packed, *vol, *det, poses, n_poses, image, nullptr, nullptr,
                                target, target_stride, (double*)workspace, s);
     if (st) return st;
-    hipLaunchKernelGGL(k_ncc_loss_finalize, dim3(n_poses), dim3(kReduceThreads), 0, s,
+    hipLaunchKernelGGL(k_ncc_loss_finalize, dim3(n_poses), dim3(final_threads<5>()), 0, s,
                        (const double*)workspace, flat_grid(*det).wg_per_pose, (double)hw, loss);
     return check_launch("ncc_loss_finalize");
 }
@@ -538,13 +538,13 @@ int32_t drr_render_l2(const void* packed, const drr_volume_desc* vol,
         st = launch_flat<kL2>(packed, *vol, *det, poses, n_poses, image, nullptr, nullptr, target,
                               target_stride, (double*)workspace, s);
         if (st) return st;
-        hipLaunchKernelGGL(k_l2_finalize<8>, dim3(n_poses), dim3(kReduceThreads), 0, s,
+        hipLaunchKernelGGL(k_l2_finalize<8>, dim3(n_poses), dim3(final_threads<8>()), 0, s,
                            (const double*)workspace, tiles, (double)hw, loss, grad_pose);
     } else {
         st = launch_flat<kL2Loss>(packed, *vol, *det, poses, n_poses, image, nullptr, nullptr,
                                   target, target_stride, (double*)workspace, s);
         if (st) return st;
-        hipLaunchKernelGGL(k_l2_finalize<1>, dim3(n_poses), dim3(kReduceThreads), 0, s,
+        hipLaunchKernelGGL(k_l2_finalize<1>, dim3(n_poses), dim3(final_threads<1>()), 0, s,
                            (const double*)workspace, tiles, (double)hw, loss, nullptr);
     }
     return check_launch("l2_finalize");

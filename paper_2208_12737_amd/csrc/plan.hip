@@ -205,10 +205,10 @@ __global__ __launch_bounds__(64 * WX * WY * G, run_waves<RUNS>()) void render_pl
 
 // Loss and pose gradient of every objective item: workgroup i reduces the
 // tile sums of item first + i in a fixed order.
-__global__ __launch_bounds__(kReduceThreads) void k_plan_ncc_finalize(
+__global__ __launch_bounds__(final_threads<kNccSums>()) void k_plan_ncc_finalize(
     const char* __restrict__ block, int group)
 {
-    __shared__ double lds[kReduceThreads * kNccSums];
+    __shared__ double lds[final_parts<kNccSums>() * kNccSums];
     const PlanHeader* hdr = (const PlanHeader*)block;
     const PlanItem* items = (const PlanItem*)(block + sizeof(PlanHeader));
     const PlanItem& it = items[hdr->first[group] + (int)blockIdx.x];
@@ -468,8 +468,8 @@ static int32_t enqueue_finalize(Slot& s, int mask, hipStream_t st)
 {
     for (int g = 0; g < kGroups; ++g) {
         if (group_mode(g) != kNcc || !(mask & (1 << g))) continue;
-        hipLaunchKernelGGL(k_plan_ncc_finalize, dim3(s.h_header->count[g]), dim3(kReduceThreads),
-                           0, st, (const char*)s.d_block, g);
+        hipLaunchKernelGGL(k_plan_ncc_finalize, dim3(s.h_header->count[g]),
+                           dim3(final_threads<kNccSums>()), 0, st, (const char*)s.d_block, g);
         const int32_t rc = check_launch("plan objective finalize");
         if (rc) return rc;
     }

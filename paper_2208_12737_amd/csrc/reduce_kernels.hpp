@@ -20,10 +20,10 @@ __device__ inline void sum_partials(const double* __restrict__ partials, int n, 
 }
 
 // grad_pose[b][j] = sum of partials (7 values per tile).
-__global__ __launch_bounds__(kReduceThreads) void k_grad_finalize(const double* partials, int n,
+__global__ __launch_bounds__(final_threads<7>()) void k_grad_finalize(const double* partials, int n,
                                                                   float* grad_pose)
 {
-    __shared__ double lds[kReduceThreads * 7];
+    __shared__ double lds[final_parts<7>() * 7];
     sum_partials<7>(partials, n, lds);
     if ((int)threadIdx.x < 7) grad_pose[blockIdx.x * 7 + threadIdx.x] = (float)lds[threadIdx.x];
 }
@@ -32,22 +32,22 @@ __global__ __launch_bounds__(kReduceThreads) void k_grad_finalize(const double* 
 //   Z = cov(I, T) / (std I std T), loss = -Z
 //   d loss / d pose = -1/(N std I) [ (S_TJ - mean T S_J) / std T
 //                                    - Z (S_IJ - mean I S_J) / std I ]
-__global__ __launch_bounds__(kReduceThreads) void k_ncc_grad_finalize(const double* partials,
+__global__ __launch_bounds__(final_threads<kNccSums>()) void k_ncc_grad_finalize(const double* partials,
                                                                       int n, double npix,
                                                                       float* loss,
                                                                       float* grad_pose)
 {
-    __shared__ double lds[kReduceThreads * kNccSums];
+    __shared__ double lds[final_parts<kNccSums>() * kNccSums];
     sum_partials<kNccSums>(partials, n, lds);
     ncc_from_sums(lds, npix, loss + blockIdx.x, grad_pose + blockIdx.x * 7);
 }
 
 // Loss only, from fused tile sums (I, I^2, T, T^2, IT): loss[b] = -Z.
-__global__ __launch_bounds__(kReduceThreads) void k_ncc_loss_finalize(const double* partials,
+__global__ __launch_bounds__(final_threads<5>()) void k_ncc_loss_finalize(const double* partials,
                                                                       int n, double npix,
                                                                       float* loss)
 {
-    __shared__ double lds[kReduceThreads * 5];
+    __shared__ double lds[final_parts<5>() * 5];
     sum_partials<5>(partials, n, lds);
     if (threadIdx.x == 0) {
         const double* S = lds;
@@ -62,11 +62,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_ncc_loss_finalize(const doub
 // ((I-T)^2 and, with NS = 8, (I-T) J[7]):
 //   loss = S_0 / N,  d loss / d pose_j = 2 S_{1+j} / N.
 template <int NS>
-__global__ __launch_bounds__(kReduceThreads) void k_l2_finalize(const double* partials, int n,
+__global__ __launch_bounds__(final_threads<NS>()) void k_l2_finalize(const double* partials, int n,
                                                                 double npix, float* loss,
                                                                 float* grad_pose)
 {
-    __shared__ double lds[kReduceThreads * NS];
+    __shared__ double lds[final_parts<NS>() * NS];
     sum_partials<NS>(partials, n, lds);
     const int j = threadIdx.x;
     if (j == 0) loss[blockIdx.x] = (float)(lds[0] / npix);
@@ -123,11 +123,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_ncc_moments(const float* __r
 }
 
 // stats[b] = (mean I, std I, mean T, std T, Z); loss[b] = -Z.
-__global__ __launch_bounds__(kReduceThreads) void k_ncc_stats(const double* partials, int n,
+__global__ __launch_bounds__(final_threads<5>()) void k_ncc_stats(const double* partials, int n,
                                                               double npix, double* stats,
                                                               float* loss)
 {
-    __shared__ double lds[kReduceThreads * 5];
+    __shared__ double lds[final_parts<5>() * 5];
     sum_partials<5>(partials, n, lds);
     if (threadIdx.x == 0) {
         const double* S = lds;
