@@ -104,6 +104,15 @@ static int32_t launch_flat(const void* packed, const drr_volume_desc& vol,
         if (blocks <= cus)
             return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFew>, 1, set >= 0 ? set : 4);
         const int wgs = run_big_tables(vol, det);
+        // up to three workgroups a CU on a volume of 6 M voxels or more wait for
+        // reads rather than for waves, and gain by the registers (gradients of
+        // 21 poses of 77 x 77 pixels on 359 x 82 x 242 voxels: 86 us, 105 us
+        // with RunFull; 16 poses of 160 x 160 on 275 x 469 x 47: 369 / 378 us);
+        // smaller volumes lose (9 of 141 x 117 on 127 x 143 x 61: 33.9 / 31.3 us)
+        if constexpr (ModeTraits<MODE>::jac)
+            if (blocks <= 3ull * cus && (double)vol.nx * vol.ny * vol.nz >= 6e6)
+                return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunWide>, 1,
+                              set >= 0 ? set : 4);
         if (wgs == 0 || blocks <= 8ull * cus)
             return launch(render_flat<8, 2, 2, MODE, kDeepDepth, RunFull>, 1, set >= 0 ? set : 4);
         const int pairs = set >= 0 ? (set + 1) / 2 : wgs;

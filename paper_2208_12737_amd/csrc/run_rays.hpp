@@ -79,8 +79,10 @@ DRR_HOST_DEVICE inline bool run_too_far(const RunAxis& x)
 
 // Axis along which the ray's runs go.  Best is the axis whose planes it
 // crosses most often; `pose` (that axis for the pose's central ray) is taken
-// while the ray crosses its planes at least half as often, so that the rays
-// of a wave agree.  Per ray and pose, so that results do not depend on which
+// while the ray crosses its planes at least a third as often, so that the rays
+// of a wave agree (half as often left more waves with two directions, whose
+// passes follow one another: the gradient of two poses of 301 x 301 pixels on
+// 88 x 247 x 149 voxels 43.6 us, a third 39.7 us, a quarter 40.0 us).  Per ray and pose, so that results do not depend on which
 // rays share a wave.
 DRR_HOST_DEVICE inline int run_direction(const double d[3], const double inv_sp[3], int pose)
 {
@@ -89,7 +91,7 @@ DRR_HOST_DEVICE inline int run_direction(const double d[3], const double inv_sp[
     const int most = (e0 >= e1 && e0 >= e2) ? 0 : (e1 >= e2 ? 1 : 2);
     const double e = pose == 0 ? e0 : (pose == 1 ? e1 : e2);
     const double m = most == 0 ? e0 : (most == 1 ? e1 : e2);
-    return pose >= 0 && 2.0 * e >= m ? pose : most;
+    return pose >= 0 && 3.0 * e >= m ? pose : most;
 }
 
 }  // namespace drr

@@ -40,6 +40,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "run_rays.hpp"
 #include "siddon.hpp"
 
@@ -59,7 +61,10 @@ namespace drr {
 //   RunFew     launches of about a wave per SIMD, which have nothing else to
 //              hide a read's latency: pairs of batches (one such DRR: 33 us
 //              with eight, 38 us with four, 39-48 us without the pipeline)
-//   RunRare    a wave's second direction: small, for its registers
+//   RunRare    a wave's second direction: small, for its registers (with
+//              RunFew, which has any number, as the first: a gradient of three
+//              poses of 154 x 119 pixels on 421 x 105 x 125 voxels, a third of
+//              its waves mixed, 31.8 us, 38.7 us with RunRare)
 template <int UNROLL, bool PIPELINED>
 struct RunShape {
     static constexpr int unroll = UNROLL;
@@ -400,7 +405,8 @@ __device__ __forceinline__ RayAcc trace_runs(const VolArgs& V, bool inside, cons
     // computes from the pose, detector and volume before it and hold that in
     // some 40 registers through the crossings; small batches, for
     // the same reason)
-    while (~done) pass(RunRare{});
+    using Rest = typename std::conditional<S::pipelined, S, RunRare>::type;
+    while (~done) pass(Rest{});
     return r;
 }
 

@@ -106,7 +106,8 @@ def test_volumes_beyond_the_tables_range_are_traced_by_the_merge(value):
         torch.testing.assert_close(a, b, **same)
 
 
-@pytest.mark.parametrize("dims,n", [((60, 50, 70), 200), ((216, 216, 220), 40)])
+@pytest.mark.parametrize("dims,n", [((60, 50, 70), 200), ((216, 216, 220), 6),
+                                    ((216, 216, 220), 40)])
 def test_launch_shapes_give_the_same_bits(dims, n):
     """A pose alone (about a wave per SIMD), in a batch of single tiles and, on
     the larger volume, in one of two tiles a workgroup with an odd number of
