@@ -1092,9 +1092,9 @@ def main():
                                                  if prof.get("traffic_bytes_per_launch") else None),
                            "measured_hbm_frac": (prof["traffic_bytes_per_launch"] / t_fwd / 8.0e12
                                                  if prof.get("traffic_bytes_per_launch") else None),
-                           "limiter": "L1 gather issue (texture addresser) and VALU issue; the "
-                                      "volume copy in use stays in the Infinity Cache, so HBM "
-                                      "traffic is below the algorithmic bytes"}
+                           "limiter": "crossing-table lines that miss the L2; a ray reads two "
+                                      "entries at some 190 plane crossings rather than 685 "
+                                      "voxels, so the algorithmic bytes can exceed the peak"}
         res["plan"] = plan_cfg
         if fresh_tune is not None:
             res["autotune_from_scratch"] = fresh_tune
@@ -1117,8 +1117,7 @@ def main():
                                   "bytes_per_launch": fb_bytes,
                                   "achieved_is": "algorithmic bytes (4 B per voxel gather + 4 B "
                                                  "per target pixel) / event-timed launch",
-                                  "limiter": "texture addresser and VALU issue together (see "
-                                             "profiles/render_ncc_grad_ct512_det256_poses256.md)"}
+                                  "limiter": "crossing-table lines that miss the L2, as the forward"}
         if "value" not in res:
             res["value"] = nb / t_fb
     res["step_p50_ms"] = float(np.percentile(step_ms, 50))

@@ -27,7 +27,7 @@ constexpr int final_threads()
 
 // Sums base[0..n)[0..NS) over the first index into lds[0..NS) (of final_parts
 // * NS doubles), in a fixed order.  Bound by the latency of its reads: four are
-// in flight (three steps of 32 registrations at 128 x 128 pixels: 193 us, 199 us
+// in flight (three steps of 16 registrations at 128 x 128 pixels: 193 us, 199 us
 // with eight, most of them past the last row).
 template <int NS>
 __device__ inline void sum_tile_partials(const double* __restrict__ base, int n, double* lds)
